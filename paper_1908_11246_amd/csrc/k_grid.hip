@@ -1,16 +1,24 @@
 // Model-matrix construction (done once per grid and model, Appendix A: the
 // N model evaluations and the sort are amortised over all propagated pdfs):
 //   k_eval_grid     f_i = M(x_i) at cell centres, FP64
-//   k_minmax / k_edges   B uniform bins over [min f, max f]
+//   k_minmax / k_edges  B uniform bins over [min f, max f]
 //   k_bin           indicator of eq. (4) as a bin index; padded bin map
 //                   (4*bin, LDS byte offsets for the sweep kernels), padded
 //                   FP32 copy of f in anchored form (every eighth column
 //                   holds f, the columns after it their offset from it),
 //                   per-chunk bin counts
-//   k_tile_sums, k_scan_tile_sums, k_tile_scan  exclusive scan of the counts in
-//                   (bin, chunk) order; k_csr_offsets  CSR row starts and counts
-//   k_scatter       stable scatter of cell indices into compressed-by-bin
-//                   order (the sparse one-hot model matrix of eq. (5))
+//   k_count         per bin the exclusive scan of its chunk counts; runs of
+//                   equal bin per row
+//   k_offsets       CSR row starts (scan over the bins), run row pointers
+//   k_fill          stable scatter of cell indices into compressed-by-bin
+//                   order (the sparse one-hot model matrix of eq. (5)); run
+//                   records and the cells' run indices
+// Each of these launches covers both the compressed-by-bin form and the run
+// form, which only depend on the bin map: at 1024^2 cells a launch's start and
+// end cost about as much as its work. (1024^2 cells, 256 bins: vup_bin's
+// kernels took 66 to 94 us in 13 launches with one launch per part, 38 us in
+// these 4; evaluation, edges, vup_bin and the choice of the form together 156
+// and 122 us of wall time.)
 // plus the per-distribution window listing.
 #include <hip/hip_runtime.h>
 
@@ -73,6 +81,11 @@ __device__ __forceinline__ double of_ord(unsigned long long o) {
   return __longlong_as_double((long long)u);
 }
 
+// Min and max of the non-NaN model values as order-preserving integer images.
+// A thread reads eight values at once (independent loads in flight), the
+// workgroup reduces in LDS and leaves its pair in edges[2 block], [2 block + 1]
+// (there are at most (B + 1) / 2 workgroups), or, with few edges, merges it
+// into edges[0] and edges[B] with atomics.
 __global__ void k_minmax_init(unsigned long long* e, int B) {
   if (threadIdx.x == 0) {
     e[0] = ~0ull;  // running min image
@@ -80,9 +93,27 @@ __global__ void k_minmax_init(unsigned long long* e, int B) {
   }
 }
 
-// Min and max of the non-NaN model values as order-preserving integer images.
-// A thread reads eight values at once (independent loads in flight), the
-// workgroup reduces in LDS, and one pair of atomics per workgroup merges.
+__device__ __forceinline__ void reduce_minmax(unsigned long long& mn, unsigned long long& mx,
+                                              unsigned long long* smn, unsigned long long* smx) {
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned long long a = __shfl_xor(mn, off, 64), b = __shfl_xor(mx, off, 64);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    smn[threadIdx.x >> 6] = mn;
+    smx[threadIdx.x >> 6] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+      mn = smn[w] < mn ? smn[w] : mn;
+      mx = smx[w] > mx ? smx[w] : mx;
+    }
+  }
+}
+
+template <bool PART>
 __global__ __launch_bounds__(256) void k_minmax(const double* __restrict__ f, long long N,
                                                 unsigned long long* e, int B) {
   __shared__ unsigned long long smn[4], smx[4];
@@ -103,33 +134,38 @@ __global__ __launch_bounds__(256) void k_minmax(const double* __restrict__ f, lo
       mx = o > mx ? o : mx;
     }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long a = __shfl_xor(mn, off, 64), b = __shfl_xor(mx, off, 64);
-    mn = a < mn ? a : mn;
-    mx = b > mx ? b : mx;
-  }
-  if ((threadIdx.x & 63) == 0) {
-    smn[threadIdx.x >> 6] = mn;
-    smx[threadIdx.x >> 6] = mx;
-  }
-  __syncthreads();
+  reduce_minmax(mn, mx, smn, smx);
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) {
-      mn = smn[w] < mn ? smn[w] : mn;
-      mx = smx[w] > mx ? smx[w] : mx;
+    if constexpr (PART) {
+      e[2 * blockIdx.x] = mn;
+      e[2 * blockIdx.x + 1] = mx;
+    } else {
+      atomicMin(e, mn);
+      atomicMax(e + B, mx);
     }
-    atomicMin(e, mn);
-    atomicMax(e + B, mx);
   }
 }
 
-__global__ __launch_bounds__(256) void k_edges(double* e, int B) {
+// parts > 0: the pairs k_minmax<true> left; 0: edges[0] and edges[B]
+__global__ __launch_bounds__(256) void k_edges(double* e, int B, int parts) {
 #pragma clang fp contract(off)
+  __shared__ unsigned long long smn[4], smx[4];
   __shared__ double lohi[2];
+  const unsigned long long* u = reinterpret_cast<const unsigned long long*>(e);
+  unsigned long long mn = ~0ull, mx = 0ull;
+  if (parts > 0) {
+    for (int p = threadIdx.x; p < parts; p += 256) {
+      mn = u[2 * p] < mn ? u[2 * p] : mn;
+      mx = u[2 * p + 1] > mx ? u[2 * p + 1] : mx;
+    }
+    reduce_minmax(mn, mx, smn, smx);
+  } else if (threadIdx.x == 0) {
+    mn = u[0];
+    mx = u[B];
+  }
   if (threadIdx.x == 0) {
-    const unsigned long long* u = reinterpret_cast<const unsigned long long*>(e);
-    lohi[0] = of_ord(u[0]);
-    lohi[1] = of_ord(u[B]);
+    lohi[0] = of_ord(mn);
+    lohi[1] = of_ord(mx);
   }
   __syncthreads();
   const double lo = lohi[0], hi = lohi[1];
@@ -139,12 +175,24 @@ __global__ __launch_bounds__(256) void k_edges(double* e, int B) {
 
 hipError_t launch_uniform_edges(const double* f, int64_t N, int B, double* edges, hipStream_t s) {
   unsigned long long* e = reinterpret_cast<unsigned long long*>(edges);
-  hipLaunchKernelGGL(k_minmax_init, dim3(1), dim3(64), 0, s, e, B);
   long long blocks = (N + 2047) / 2048;  // eight values per thread
   if (blocks > 1024) blocks = 1024;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_minmax, dim3((unsigned)blocks), dim3(256), 0, s, f, (long long)N, e, B);
-  hipLaunchKernelGGL(k_edges, dim3(1), dim3(256), 0, s, edges, B);
+  // the edges themselves hold the workgroups' pairs when there is room for a
+  // quarter of the workgroups: two launches and no atomics (at 2^20 cells and
+  // 256 bins 7.5 + 2.8 us; 1.4 + 9.4 + 2.4 us with atomics and one value in
+  // flight per thread)
+  long long parts = (B + 1) / 2 < blocks ? (B + 1) / 2 : blocks;
+  if (4 * parts >= blocks || parts >= 128) {
+    hipLaunchKernelGGL(k_minmax<true>, dim3((unsigned)parts), dim3(256), 0, s, f, (long long)N, e,
+                       B);
+  } else {
+    parts = 0;
+    hipLaunchKernelGGL(k_minmax_init, dim3(1), dim3(64), 0, s, e, B);
+    hipLaunchKernelGGL(k_minmax<false>, dim3((unsigned)blocks), dim3(256), 0, s, f, (long long)N,
+                       e, B);
+  }
+  hipLaunchKernelGGL(k_edges, dim3(1), dim3(256), 0, s, edges, B, (int)parts);
   return hipGetLastError();
 }
 
@@ -169,9 +217,18 @@ struct BinArgs {
 };
 
 // bin index of y: largest b < B with e[b] <= y, when e[0] <= y <= e[B]
-__device__ __forceinline__ int bin_search(const double* e, int B, double y) {
+// (inv: B over the span of the edges; a finite positive number)
+__device__ __forceinline__ int bin_search(const double* e, int B, double inv, double y) {
   if (!(y >= e[0] && y <= e[B])) return -1;
+  // where uniform edges would have it, when that is right
   int lo = 0, hi = B - 1;  // answer in [lo, hi]
+  const int g = min((int)((y - e[0]) * inv), B - 1);
+  if (e[g] <= y) {
+    if (y < e[g + 1]) return g;
+    lo = g;
+  } else {
+    hi = g - 1;
+  }
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (e[mid] <= y) lo = mid;
@@ -197,11 +254,13 @@ __global__ __launch_bounds__(256) void k_bin(BinArgs a) {
   __syncthreads();
   if (blockIdx.x == 0) {
     for (int b = threadIdx.x; b <= a.B; b += 256) a.edges_ws[b] = e[b];
-    if (threadIdx.x == 0 && bad) atomicAdd(a.counters + kCntBadEdges, 1ull);
+    // the counters start here (cells without a bin and runs follow)
+    if (threadIdx.x < 8) a.counters[threadIdx.x] = threadIdx.x == kCntBadEdges && bad ? 1ull : 0ull;
   }
+  const double span = e[a.B] - e[0];
+  const double inv = span > 0.0 && span < 1e300 && span > 1e-280 ? a.B / span : 0.0;
   const long long base = (long long)blockIdx.x * a.chunk;
   const long long total = a.rows * a.pitch;
-  int outside = 0;
   for (int q = threadIdx.x; q < a.chunk; q += 256) {
     const long long p = base + q;
     if (p >= total) break;
@@ -212,13 +271,12 @@ __global__ __launch_bounds__(256) void k_bin(BinArgs a) {
     if (col < a.nL) {
       const long long cell = row * a.nL + col;
       const double y = a.f[cell];
-      const int b = bad ? -1 : bin_search(e, a.B, y);
+      const int b = bad ? -1 : bin_search(e, a.B, inv, y);
       if (a.bin) a.bin[cell] = b;
       if (b >= 0) {
         code = (uint16_t)(4 * b);
         atomicAdd(&cnt[b], 1);
       } else {
-        ++outside;
         atomicAdd(&cnt[a.B], 1);
       }
       // anchored FP32 form: columns 8m hold f, the seven after each their
@@ -231,8 +289,6 @@ __global__ __launch_bounds__(256) void k_bin(BinArgs a) {
     a.binmap[p] = code;
     a.f32[p] = fv;
   }
-  for (int off = 32; off > 0; off >>= 1) outside += __shfl_xor(outside, off, 64);
-  if ((threadIdx.x & 63) == 0 && outside) atomicAdd(a.counters + kCntOutside, (unsigned long long)outside);
   __syncthreads();
   for (int b = threadIdx.x; b <= a.B; b += 256) a.chunk_counts[(long long)b * a.nblk + blockIdx.x] = cnt[b];
 }
@@ -326,105 +382,6 @@ hipError_t launch_scan_excl(int* v, long long n, long long* tsum, int* total, hi
   hipLaunchKernelGGL(k_scan_tile_sums, dim3(1), dim3(1024), 0, s, tsum, nt, total);
   hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)nt), dim3(256), 0, s, v, n, tsum);
   return hipGetLastError();
-}
-
-// CSR of the model matrix from the scanned chunk counts: bin b occupies
-// [b*nblk, (b+1)*nblk) in (bin, chunk) order, so its first position is the
-// row start; slot B collects the cells without a bin, after all binned cells.
-__global__ __launch_bounds__(256) void k_csr_offsets(const int* __restrict__ cc, long long nblk,
-                                                     int B, long long N, long long* counts,
-                                                     long long* offsets) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b > B) return;
-  const long long start = cc[(long long)b * nblk];
-  const long long next = b < B ? (long long)cc[(long long)(b + 1) * nblk] : N;
-  offsets[b] = start;
-  counts[b] = next - start;
-}
-
-// one wave per chunk: cells in increasing order, stable within each bin
-__global__ __launch_bounds__(64) void k_scatter(BinArgs a, const int* __restrict__ cc,
-                                                int32_t* __restrict__ perm) {
-  extern __shared__ int pos[];  // [B+1] running positions of this chunk
-  for (int b = threadIdx.x; b <= a.B; b += 64) pos[b] = cc[(long long)b * a.nblk + blockIdx.x];
-  __syncthreads();
-  const long long base = (long long)blockIdx.x * a.chunk;
-  const long long total = a.rows * a.pitch;
-  const int lane = threadIdx.x;
-  for (int q0 = 0; q0 < a.chunk; q0 += 64) {
-    const long long p = base + q0 + lane;
-    int b = -2;
-    long long cell = -1;
-    if (p < total) {
-      const long long row = p / a.pitch;
-      const int col = (int)(p - row * a.pitch);
-      if (col < a.nL) {
-        cell = row * a.nL + col;
-        const int code = a.binmap[p];
-        b = (code == 4 * a.B) ? -2 : code >> 2;
-      }
-    }
-    // lanes holding the same bin as this lane (found one distinct bin at a
-    // time with ballots), then one LDS read of the bin's position per lane;
-    // the highest lane of each bin advances it. One wave per workgroup: its
-    // LDS reads and writes take effect in program order, so no barrier.
-    unsigned long long todo = __ballot(b >= 0), same = 0ull;
-    while (todo) {
-      const int leader = __ffsll((long long)todo) - 1;
-      const int bl = __builtin_amdgcn_readlane(b, leader);
-      const unsigned long long m = __ballot(b == bl);
-      if (b == bl) same = m;
-      todo &= ~m;
-    }
-    if (b >= 0) {
-      const int start = pos[b];
-      perm[start + __popcll(same & ((1ull << lane) - 1ull))] = (int32_t)cell;
-      if ((same >> lane) == 1ull) pos[b] = start + __popcll(same);
-    }
-  }
-}
-
-hipError_t launch_runs(const vup_mm& mm, hipStream_t s);
-
-hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, int32_t* bin,
-                      hipStream_t s) {
-  char* ws = static_cast<char*>(mm.ws);
-  WsLayout L;
-  ws_layout(mm.grid, mm.B, &L);
-  BinArgs a{};
-  a.f = f;
-  a.edges_in = edges;
-  a.edges_ws = reinterpret_cast<double*>(ws + mm.off_edges);
-  a.bin = bin;
-  a.binmap = reinterpret_cast<uint16_t*>(ws + mm.off_binmap);
-  a.f32 = reinterpret_cast<float*>(ws + mm.off_f32);
-  a.chunk_counts = reinterpret_cast<int*>(ws + mm.off_scratch);
-  a.counters = reinterpret_cast<unsigned long long*>(ws + mm.off_counters);
-  a.B = mm.B;
-  a.nL = mm.grid.n[mm.grid.ndim - 1];
-  a.pitch = mm.pitch;
-  a.rows = mm.rows;
-  a.nblk = L.nblk;
-  a.chunk = L.chunk;
-  const size_t lds = (size_t)(mm.B + 1) * 8 + (size_t)(mm.B + 1) * 4;
-  hipLaunchKernelGGL(k_bin, dim3((unsigned)L.nblk), dim3(256), lds, s, a);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  const long long nc = (long long)(mm.B + 1) * L.nblk;
-  err = launch_scan_excl(a.chunk_counts, nc, reinterpret_cast<long long*>(ws + L.off_tsum), nullptr,
-                         s);
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_csr_offsets, dim3((unsigned)((mm.B + 1 + 255) / 256)), dim3(256), 0, s,
-                     a.chunk_counts, L.nblk, mm.B, (long long)mm.N,
-                     reinterpret_cast<long long*>(ws + mm.off_counts),
-                     reinterpret_cast<long long*>(ws + mm.off_offsets));
-  err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_scatter, dim3((unsigned)L.nblk), dim3(64), (size_t)(mm.B + 1) * 4, s, a,
-                     a.chunk_counts, reinterpret_cast<int32_t*>(ws + mm.off_perm));
-  err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  return launch_runs(mm, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -525,18 +482,29 @@ bool ws_layout(const vup_grid& g, int B, WsLayout* out) {
 }
 
 // ---------------------------------------------------------------------------
-// runs of equal bin along the fastest axis (a run-length form of the model
-// matrix's rows). One thread per (row, 32-cell block).
+// the compressed-by-bin form and the runs of equal bin along the fastest axis
+// (a run-length form of the model matrix's rows), from the bin map
 // ---------------------------------------------------------------------------
-struct RunArgs {
-  const uint16_t* binmap;
+struct FormArgs {
+  const uint16_t* __restrict__ binmap;
+  // compressed by bin
+  int* cc;             // [(B+1) * nblk] chunk counts, bin-major; scanned per bin
+  long long* counts;   // [B+1]
+  long long* offsets;  // [B+1]
+  int32_t* perm;
+  int B;
+  long long nblk;
+  int chunk;
+  // runs
   uint32_t* runs;
-  int* rowptr;
+  int* rowptr;         // [rows + 1]: runs and a terminator per row, then their scan
   uint16_t* runidx;
-  int* blockcnt;       // [rows * nb] counts, then exclusive positions
   unsigned long long* counters;
   long long rows;
-  int nL, pitch, nb, none;
+  int nL, pitch, nb;   // nb 32-cell blocks per row
+  int group;           // lanes per row: a power of two, at least nb up to 64
+  int rowblocks;       // workgroups of the run part
+  int scan_rows;       // k_offsets scans the row pointers too
 };
 
 // the 32 bin codes of block q of a row (the row pitch is a multiple of 32
@@ -580,33 +548,159 @@ __device__ __forceinline__ uint32_t run_starts(const Block32& b, int q, int nL) 
   return m;
 }
 
-__global__ __launch_bounds__(256) void k_runs_count(RunArgs a) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  unsigned long long real = 0;
-  if (t < a.rows * a.nb) {
-    const long long r = t / a.nb;
-    const int q = (int)(t - r * a.nb);
-    const Block32 blk = load_block32(a.binmap + r * a.pitch, q);
-    int cnt = __popc(run_starts(blk, q, a.nL));
-    real = cnt;
-    if (q == a.nb - 1) ++cnt;  // terminator of the row
-    a.blockcnt[t] = cnt;
+// Workgroups 0 .. B: bin b's chunk counts, scanned (exclusive) in place, and
+// its total. The others: `group` lanes per row count the row's runs.
+__global__ __launch_bounds__(256) void k_count(FormArgs a) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if ((int)blockIdx.x <= a.B) {
+    __shared__ int wsum[2][4];
+    int* v = a.cc + (long long)blockIdx.x * a.nblk;
+    int carry = 0;  // uniform
+    int odd = 0;
+    for (long long p0 = 0; p0 < a.nblk; p0 += 1024, odd ^= 1) {
+      // a thread takes four consecutive chunks (their first need not be
+      // 16-byte aligned)
+      const long long p = p0 + 4 * (int)threadIdx.x;
+      int x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = p + u < a.nblk ? v[p + u] : 0;
+      int incl = (x[0] + x[1]) + (x[2] + x[3]);
+      const int own = incl;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+      }
+      if (lane == 63) wsum[odd][w] = incl;
+      __syncthreads();
+      int run = carry + incl - own;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q < w) run += wsum[odd][q];
+        carry += wsum[odd][q];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (p + u < a.nblk) v[p + u] = run;
+        run += x[u];
+      }
+    }
+    if (threadIdx.x == 0) a.counts[blockIdx.x] = carry;
+    return;
   }
-  for (int o = 32; o > 0; o >>= 1) real += __shfl_xor(real, o, 64);
-  if ((threadIdx.x & 63) == 0 && real) atomicAdd(a.counters + kCntRuns, real);
+  const long long t = (long long)(blockIdx.x - a.B - 1) * 256 + threadIdx.x;
+  const long long r = t / a.group;
+  if (r >= a.rows) return;  // whole groups
+  int cnt = 0;
+  for (int q = (int)(t % a.group); q < a.nb; q += a.group)
+    cnt += __popc(run_starts(load_block32(a.binmap + r * a.pitch, q), q, a.nL));
+  for (int o = a.group >> 1; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+  if (t % a.group == 0) a.rowptr[r] = cnt + 1;  // the row's terminator
 }
 
-__global__ __launch_bounds__(256) void k_runs_fill(RunArgs a) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= a.rows * a.nb) return;
-  const long long r = t / a.nb;
-  const int q = (int)(t - r * a.nb);
-  const uint16_t* row = a.binmap + r * a.pitch;
-  const Block32 blk = load_block32(row, q);
-  const uint32_t starts = run_starts(blk, q, a.nL);
-  const int rowstart = a.blockcnt[r * a.nb];
-  int pos = a.blockcnt[t];
-  if (q == 0) a.rowptr[r] = rowstart;
+// exclusive scan of n values by one workgroup of 1024 threads; returns the sum
+template <typename T>
+__device__ __forceinline__ long long scan_block(const T* in, T* out, long long n, long long* wsum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  long long carry = 0;
+  for (long long p0 = 0; p0 < n; p0 += 4096) {
+    const long long p = p0 + 4 * (int)threadIdx.x;
+    long long x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = p + u < n ? (long long)in[p + u] : 0;
+    const long long own = (x[0] + x[1]) + (x[2] + x[3]);
+    long long incl = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const long long t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    long long run = carry + incl - own;
+    for (int q = 0; q < 16; ++q) {
+      if (q < w) run += wsum[q];
+      carry += wsum[q];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p + u < n) out[p + u] = (T)run;
+      run += x[u];
+    }
+  }
+  return carry;
+}
+
+// workgroup 0: CSR row starts from the bins' counts; workgroup 1: run row
+// pointers. The run and outside counts go to the counters.
+__global__ __launch_bounds__(1024) void k_offsets(FormArgs a) {
+  __shared__ long long wsum[16];
+  if (blockIdx.x == 0) {
+    scan_block(a.counts, a.offsets, (long long)a.B + 1, wsum);
+    if (threadIdx.x == 0) a.counters[kCntOutside] = (unsigned long long)a.counts[a.B];
+  } else {
+    long long total;
+    if (a.scan_rows) {
+      total = scan_block(a.rowptr, a.rowptr, a.rows, wsum);
+      if (threadIdx.x == 0) a.rowptr[a.rows] = (int)total;
+    } else {
+      total = a.rowptr[a.rows];  // scanned by launch_scan_excl
+    }
+    if (threadIdx.x == 0) a.counters[kCntRuns] = (unsigned long long)(total - a.rows);
+  }
+}
+
+// one wave per chunk: cells in increasing order, stable within each bin
+__device__ __forceinline__ void scatter_chunk(const FormArgs& a, long long c, int* pos) {
+  const int lane = threadIdx.x & 63;
+  for (int b = lane; b <= a.B; b += 64)
+    pos[b] = (int)a.offsets[b] + a.cc[(long long)b * a.nblk + c];
+  const long long base = c * a.chunk;
+  const long long total = a.rows * a.pitch;
+  long long row = (base + lane) / a.pitch;
+  int col = (int)(base + lane - row * a.pitch);
+  constexpr int kAhead = 16;  // codes of 16 steps in flight
+  for (int q0 = 0; q0 < a.chunk; q0 += 64 * kAhead) {
+    int code[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const long long p = base + q0 + 64 * u + lane;
+      code[u] = q0 + 64 * u < a.chunk && p < total ? (int)a.binmap[p] : 4 * a.B;
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int cell = (int)(row * a.nL + col);
+      const int b = code[u] == 4 * a.B || col >= a.nL ? -2 : code[u] >> 2;
+      col += 64;
+      while (col >= a.pitch) {
+        col -= a.pitch;
+        ++row;
+      }
+      // lanes holding the same bin as this lane (found one distinct bin at a
+      // time with ballots), then one LDS read of the bin's position per lane;
+      // the highest lane of each bin advances it. The wave has its positions
+      // to itself: its LDS reads and writes take effect in program order, so
+      // no barrier.
+      unsigned long long todo = __ballot(b >= 0), same = 0ull;
+      while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const int bl = __builtin_amdgcn_readlane(b, leader);
+        const unsigned long long m = __ballot(b == bl);
+        if (b == bl) same = m;
+        todo &= ~m;
+      }
+      if (b >= 0) {
+        const int start = pos[b];
+        a.perm[start + __popcll(same & ((1ull << lane) - 1ull))] = (int32_t)cell;
+        if ((same >> lane) == 1ull) pos[b] = start + __popcll(same);
+      }
+    }
+  }
+}
+
+// run records and run indices of the 32 cells of block q of row r; pos: the
+// block's first record
+__device__ __forceinline__ void fill_runs(const FormArgs& a, long long r, int q, const Block32& blk,
+                                          uint32_t starts, int rowstart, int pos) {
   int cur = pos - 1 - rowstart;  // run holding the cell before this block
   uint32_t idx[16];              // run indices of the 32 cells, two per word
 #pragma unroll
@@ -618,7 +712,7 @@ __global__ __launch_bounds__(256) void k_runs_fill(RunArgs a) {
       ++pos;
     } else if (c == a.nL) {
       // terminator: first column past the row, no bin
-      a.runs[pos] = (uint32_t)a.nL | ((uint32_t)a.none << 16);
+      a.runs[pos] = (uint32_t)a.nL | ((uint32_t)(4 * a.B) << 16);
       cur = pos - rowstart;
       ++pos;
     }
@@ -631,63 +725,118 @@ __global__ __launch_bounds__(256) void k_runs_fill(RunArgs a) {
     out[i] = make_uint4(idx[4 * i], idx[4 * i + 1], idx[4 * i + 2], idx[4 * i + 3]);
   if (q == a.nb - 1 && a.nL == a.nb * 32) {
     // row length is a multiple of 32: terminator after the last block
-    a.runs[pos] = (uint32_t)a.nL | ((uint32_t)a.none << 16);
+    a.runs[pos] = (uint32_t)a.nL | ((uint32_t)(4 * a.B) << 16);
   }
 }
 
-__global__ void k_rowptr_end(int* rowptr, long long rows, const int* total) {
-  if (threadIdx.x == 0) rowptr[rows] = *total;
+// the first workgroups fill the runs (`group` lanes per row), the others
+// scatter (a wave per chunk)
+__global__ __launch_bounds__(256) void k_fill(FormArgs a) {
+  extern __shared__ int pos[];  // [waves][B+1] running positions of the chunks
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if ((int)blockIdx.x >= a.rowblocks) {
+    const long long c = (long long)(blockIdx.x - a.rowblocks) * (blockDim.x >> 6) + w;
+    if (c < a.nblk) scatter_chunk(a, c, pos + w * (a.B + 1));
+    return;
+  }
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long r = t / a.group;
+  const bool in = r < a.rows;
+  const int g = lane & (a.group - 1);
+  const int rowstart = in ? a.rowptr[r] : 0;
+  int carry = rowstart;
+  for (int q0 = 0; q0 < a.nb; q0 += a.group) {
+    const int q = q0 + g;
+    Block32 blk = {};
+    uint32_t starts = 0;
+    if (in && q < a.nb) {
+      blk = load_block32(a.binmap + r * a.pitch, q);
+      starts = run_starts(blk, q, a.nL);
+    }
+    const int cnt = __popc(starts);
+    int incl = cnt;
+    for (int o = 1; o < a.group; o <<= 1) {
+      const int x = __shfl_up(incl, o, a.group);
+      if (g >= o) incl += x;
+    }
+    if (in && q < a.nb) fill_runs(a, r, q, blk, starts, rowstart, carry + incl - cnt);
+    carry += __shfl(incl, a.group - 1, a.group);
+  }
+}
+
+hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, int32_t* bin,
+                      hipStream_t s) {
+  char* ws = static_cast<char*>(mm.ws);
+  WsLayout L;
+  ws_layout(mm.grid, mm.B, &L);
+  BinArgs a{};
+  a.f = f;
+  a.edges_in = edges;
+  a.edges_ws = reinterpret_cast<double*>(ws + mm.off_edges);
+  a.bin = bin;
+  a.binmap = reinterpret_cast<uint16_t*>(ws + mm.off_binmap);
+  a.f32 = reinterpret_cast<float*>(ws + mm.off_f32);
+  a.chunk_counts = reinterpret_cast<int*>(ws + mm.off_scratch);
+  a.counters = reinterpret_cast<unsigned long long*>(ws + mm.off_counters);
+  a.B = mm.B;
+  a.nL = mm.grid.n[mm.grid.ndim - 1];
+  a.pitch = mm.pitch;
+  a.rows = mm.rows;
+  a.nblk = L.nblk;
+  a.chunk = L.chunk;
+  const size_t lds = (size_t)(mm.B + 1) * 8 + (size_t)(mm.B + 1) * 4;
+  hipLaunchKernelGGL(k_bin, dim3((unsigned)L.nblk), dim3(256), lds, s, a);
+  FormArgs m{};
+  m.binmap = a.binmap;
+  m.cc = a.chunk_counts;
+  m.counts = reinterpret_cast<long long*>(ws + mm.off_counts);
+  m.offsets = reinterpret_cast<long long*>(ws + mm.off_offsets);
+  m.perm = reinterpret_cast<int32_t*>(ws + mm.off_perm);
+  m.B = mm.B;
+  m.nblk = L.nblk;
+  m.chunk = L.chunk;
+  m.runs = reinterpret_cast<uint32_t*>(ws + mm.off_runs);
+  m.rowptr = reinterpret_cast<int*>(ws + mm.off_rowptr);
+  m.runidx = reinterpret_cast<uint16_t*>(ws + mm.off_runidx);
+  m.counters = a.counters;
+  m.rows = mm.rows;
+  m.nL = a.nL;
+  m.pitch = a.pitch;
+  m.nb = a.pitch / 32;
+  m.group = 1;
+  while (m.group < m.nb && m.group < 64) m.group *= 2;
+  // one workgroup scans up to 16384 row pointers in four steps (12.4 us, 3.1
+  // us at 1024 rows); more take three launches over many workgroups (13.8 us
+  // at 110592 rows), where one workgroup would take 27 steps
+  m.scan_rows = mm.rows <= 16384;
+  const long long rowthreads = mm.rows * m.group;
+  hipLaunchKernelGGL(k_count, dim3((unsigned)(mm.B + 1 + (rowthreads + 255) / 256)), dim3(256), 0,
+                     s, m);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  if (!m.scan_rows) {
+    err = launch_scan_excl(m.rowptr, mm.rows, reinterpret_cast<long long*>(ws + L.off_tsum),
+                           m.rowptr + mm.rows, s);
+    if (err != hipSuccess) return err;
+  }
+  hipLaunchKernelGGL(k_offsets, dim3(2), dim3(1024), 0, s, m);
+  // four chunks per workgroup while their positions fit in 64 KB of LDS
+  const int waves = (size_t)(mm.B + 1) * 16 <= 65536 ? 4 : 2;
+  m.rowblocks = (int)((rowthreads + 64 * waves - 1) / (64 * waves));
+  const long long blocks = m.rowblocks + (L.nblk + waves - 1) / waves;
+  hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(64 * waves),
+                     (size_t)(mm.B + 1) * 4 * waves, s, m);
+  return hipGetLastError();
 }
 
 __global__ void k_set_mode(unsigned long long* counters, int mode) {
   if (threadIdx.x == 0) counters[kCntMode] = (unsigned long long)mode;
 }
 
-// zero the model matrix's counters (8 words) with a kernel rather than a
-// memset, so that a caller may capture vup_bin in a graph
-__global__ void k_clear_counters(unsigned long long* counters) {
-  if (threadIdx.x < 8) counters[threadIdx.x] = 0ull;
-}
-
-hipError_t launch_clear_counters(void* counters, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_counters, dim3(1), dim3(64), 0, s,
-                     static_cast<unsigned long long*>(counters));
-  return hipGetLastError();
-}
-
 hipError_t launch_set_mode(const vup_mm& mm, int mode, hipStream_t s) {
   unsigned long long* c =
       reinterpret_cast<unsigned long long*>(static_cast<char*>(mm.ws) + mm.off_counters);
   hipLaunchKernelGGL(k_set_mode, dim3(1), dim3(64), 0, s, c, mode);
-  return hipGetLastError();
-}
-
-hipError_t launch_runs(const vup_mm& mm, hipStream_t s) {
-  char* ws = static_cast<char*>(mm.ws);
-  RunArgs a{};
-  a.binmap = reinterpret_cast<const uint16_t*>(ws + mm.off_binmap);
-  a.runs = reinterpret_cast<uint32_t*>(ws + mm.off_runs);
-  a.rowptr = reinterpret_cast<int*>(ws + mm.off_rowptr);
-  a.runidx = reinterpret_cast<uint16_t*>(ws + mm.off_runidx);
-  a.blockcnt = reinterpret_cast<int*>(ws + mm.off_scratch);
-  a.counters = reinterpret_cast<unsigned long long*>(ws + mm.off_counters);
-  a.rows = mm.rows;
-  a.nL = mm.grid.n[mm.grid.ndim - 1];
-  a.pitch = mm.pitch;
-  a.nb = mm.pitch / 32;
-  a.none = 4 * mm.B;
-  const long long n = a.rows * a.nb;
-  const unsigned blocks = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(k_runs_count, dim3(blocks), dim3(256), 0, s, a);
-  WsLayout L;
-  ws_layout(mm.grid, mm.B, &L);
-  const hipError_t err =
-      launch_scan_excl(a.blockcnt, n, reinterpret_cast<long long*>(ws + L.off_tsum),
-                       reinterpret_cast<int*>(a.counters + kCntScratch), s);
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_runs_fill, dim3(blocks), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_rowptr_end, dim3(1), dim3(64), 0, s, a.rowptr, a.rows,
-                     reinterpret_cast<const int*>(a.counters + kCntScratch));
   return hipGetLastError();
 }
 

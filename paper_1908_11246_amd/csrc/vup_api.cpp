@@ -186,9 +186,7 @@ int vup_bin(const vup_grid* g, const double* f, const double* edges, int32_t B, 
   mm.reserved = 0;
   mm.magic = vup::kMagic;
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e = vup::launch_clear_counters(static_cast<char*>(ws) + L.off_counters, s);
-  if (e != hipSuccess) return launched(e, "vup_bin (clear counters)");
-  e = vup::launch_bin(mm, f, edges, bin, s);
+  const hipError_t e = vup::launch_bin(mm, f, edges, bin, s);
   if (e != hipSuccess) return launched(e, "vup_bin");
   *mm_out = mm;
   return ok();
@@ -337,16 +335,21 @@ int vup_set_sweep_mode(vup_mm* mm, int32_t mode, void* stream) {
   if ((r = check_device())) return r;
   hipStream_t s = (hipStream_t)stream;
   if (mode == VUP_SWEEP_AUTO) {
-    // resolve now from the run count vup_bin left in the counters
+    // resolve now from the run count vup_bin left in the counters (the copy
+    // follows the stream's work)
     const char* c = static_cast<const char*>(mm->ws) + mm->off_counters;
-    int64_t nruns = 0;
-    hipError_t e = hipStreamSynchronize(s);
-    if (e == hipSuccess)
-      e = hipMemcpy(&nruns, c + vup::kCntRuns * sizeof(int64_t), sizeof(nruns),
-                    hipMemcpyDeviceToHost);
+    int64_t cnt[8] = {};
+    hipError_t e = hipMemcpyAsync(cnt, c, sizeof cnt, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return launched(e, "vup_set_sweep_mode");
+    const int64_t nruns = cnt[vup::kCntRuns];
     const bool runs = vup::runs_allowed(*mm) && nruns > 0 && nruns * vup::kRunMinLength <= mm->N;
     mode = runs ? VUP_SWEEP_RUNS : VUP_SWEEP_CELLS;
+    // the device follows the same rule while no form was forced on it
+    if (cnt[vup::kCntMode] == VUP_SWEEP_AUTO) {
+      mm->sweep = mode;
+      return ok();
+    }
   }
   mm->sweep = mode;
   return launched(vup::launch_set_mode(*mm, mode, s), "vup_set_sweep_mode");

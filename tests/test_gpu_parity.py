@@ -1063,6 +1063,45 @@ def test_run_structure_bitexact(vup, orc, n):
         assert np.array_equal(ri[r, :n[-1]], ref)
 
 
+@pytest.mark.parametrize("n,B,even", [
+    ((3, 5), 1, True),             # fewer cells than a workgroup's share, one bin
+    ((33, 2050), 7, True),         # rows of more than 64 blocks, atomics for min and max
+    ((17, 9, 110, 3), 300, True),  # more rows than one workgroup scans
+    ((70, 1000), 4096, True),      # most bins: two chunks per scatter workgroup
+    ((70, 1000), 4096, False),     # uneven edges, cells outside them, NaN cells
+    ((300, 301), 50, False),
+])
+def test_built_forms_bitexact(vup, orc, n, B, even):
+    rng = np.random.default_rng(B)
+    d = len(n)
+    f = rng.normal(size=int(np.prod(n)))
+    f[rng.random(f.size) < 0.5] = 0.25  # long runs next to short ones
+    if even:
+        eo = orc.uniform_edges(f, B)
+    else:
+        f[::97] = np.nan
+        eo = np.sort(rng.normal(size=B + 1) ** 3)
+    g = vup.make_grid(n, (-1.0,) * d, (1.0,) * d)
+    ft = torch.from_numpy(f).to(DEV)
+    if even:
+        assert np.array_equal(_cpu(vup.uniform_edges(ft, B)), eo)
+    mm = vup.build_model_matrix(g, ft, torch.from_numpy(eo).to(DEV))
+    bo = orc.bins(f, eo)
+    assert np.array_equal(_cpu(mm.bin), bo)
+    key = np.where(bo < 0, B, bo)
+    counts = np.bincount(key, minlength=B + 1)
+    assert np.array_equal(_cpu(mm.counts), counts)
+    assert np.array_equal(_cpu(mm.offsets), np.r_[0, np.cumsum(counts)[:-1]])
+    inside = int(counts[:B].sum())
+    assert np.array_equal(_cpu(mm.perm)[:inside], np.argsort(key, kind="stable")[:inside])
+    recs, ptr, idx = _runs_reference(bo.reshape(-1, n[-1]), B)
+    assert np.array_equal(_cpu(mm.rowptr), ptr)
+    assert np.array_equal((_cpu(mm.runs).astype(np.int64) & 0xFFFFFFFF)[:len(recs)], recs)
+    ri = _cpu(mm.runidx).astype(np.int64).reshape(-1, mm.mm.pitch)
+    for r, ref in enumerate(idx):
+        assert np.array_equal(ri[r, :n[-1]], ref)
+
+
 def test_run_and_cell_forms_agree(vup, orc):
     for wl in (workloads.grid64(), workloads.grid1024().subset(workloads.sample_indices(65536, 40, 9)),
                workloads.random_workload("runs2d", (57, 300), (-3, -3), (3, 3), "sincos2", 40, 60, 2,
