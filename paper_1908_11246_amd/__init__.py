@@ -100,6 +100,10 @@ def _load():
                             _P(VupMM), _vp]
     lib.vup_windows.argtypes = [_P(VupGrid), _P(VupDists), _vp, _vp]
     lib.vup_propagate.argtypes = [_P(VupMM), _P(VupDists), ctypes.c_int32, _vp, _vp, _vp]
+    lib.vup_propagate_tiled_workspace_bytes.restype = ctypes.c_size_t
+    lib.vup_propagate_tiled_workspace_bytes.argtypes = [_P(VupMM), _P(VupDists), ctypes.c_int32]
+    lib.vup_propagate_tiled.argtypes = [_P(VupMM), _P(VupDists), ctypes.c_int32, _vp,
+                                        ctypes.c_size_t, _vp, _vp, _vp]
     lib.vup_moments.argtypes = [_P(VupMM), _P(VupDists), _P(VupModel), _vp, _vp, _vp, _vp]
     lib.vup_moments_tiled_workspace_bytes.restype = ctypes.c_size_t
     lib.vup_moments_tiled_workspace_bytes.argtypes = [_P(VupMM), _P(VupDists)]
@@ -326,8 +330,16 @@ def propagate(mm: ModelMatrix, mu, sigma, weight=None, precision: str = "fp32",
     P = out if out is not None else torch.empty((K, mm.B), dtype=torch.float32, device=mm.device)
     Z = torch.empty((K, C), dtype=torch.float64, device=mm.device) if want_Z else None
     d = _dists(mu, sigma, w, n_sigma)
-    _check(_load().vup_propagate(ctypes.byref(mm.mm), ctypes.byref(d), PRECISIONS[precision],
-                                 _ptr(P), _ptr(Z), _vp(_stream())))
+    lib = _load()
+    mref, dref, prec = ctypes.byref(mm.mm), ctypes.byref(d), PRECISIONS[precision]
+    # large sets of pdfs on 2-D grids are swept by tiles, which takes a workspace
+    nb = lib.vup_propagate_tiled_workspace_bytes(mref, dref, prec) if K >= 16384 else 0
+    if nb:
+        ws = torch.empty(nb, dtype=torch.uint8, device=mm.device)
+        _check(lib.vup_propagate_tiled(mref, dref, prec, _ptr(ws), nb, _ptr(P), _ptr(Z),
+                                       _vp(_stream())))
+    else:
+        _check(lib.vup_propagate(mref, dref, prec, _ptr(P), _ptr(Z), _vp(_stream())))
     return P, Z
 
 

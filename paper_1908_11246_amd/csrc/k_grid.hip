@@ -12,16 +12,18 @@
 //   k_offsets       CSR row starts (scan over the bins), run row pointers
 //   k_fill          stable scatter of cell indices into compressed-by-bin
 //                   order (the sparse one-hot model matrix of eq. (5)); run
-//                   records and the cells' run indices
+//                   records and the cells' run indices; on 2-D grids the
+//                   tiled propagation's entries (k_ptiles.hpp)
 // Each of these launches covers both the compressed-by-bin form and the run
 // form, which only depend on the bin map: at 1024^2 cells a launch's start and
 // end cost about as much as its work. (1024^2 cells, 256 bins: vup_bin's
-// kernels took 66 to 94 us in 13 launches with one launch per part, 38 us in
-// these 4; evaluation, edges, vup_bin and the choice of the form together 156
-// and 122 us of wall time.)
+// kernels took 66 to 94 us in 13 launches with one launch per part, 41 us in
+// these 4, with the entries, which took 20 us by themselves; evaluation, edges,
+// vup_bin and the choice of the form together 158 and 122 us of wall time.)
 // plus the per-distribution window listing.
 #include <hip/hip_runtime.h>
 
+#include "k_ptiles.hpp"
 #include "vup_device.hpp"
 #include "vup_internal.hpp"
 
@@ -476,6 +478,16 @@ bool ws_layout(const vup_grid& g, int B, WsLayout* out) {
   o = align256(o + (size_t)(L.rows + 1) * 4);
   L.off_runidx = o;
   o = align256(o + (size_t)padded * 2);
+  if (g.ndim == 2) {
+    size_t ents, chunks, blocks;
+    tile_entry_sizes(g, &ents, &chunks, &blocks);
+    L.off_tents = o;
+    o = align256(o + ents);
+    L.off_tchunks = o;
+    o = align256(o + chunks);
+    L.off_tblocks = o;
+    o = align256(o + blocks);
+  }
   L.bytes = o;
   *out = L;
   return true;
@@ -504,7 +516,11 @@ struct FormArgs {
   int nL, pitch, nb;   // nb 32-cell blocks per row
   int group;           // lanes per row: a power of two, at least nb up to 64
   int rowblocks;       // workgroups of the run part
+  int swaves;          // chunks per workgroup of the scatter
   int scan_rows;       // k_offsets scans the row pointers too
+  // entries of the tiled propagation (2-D grids)
+  int entblocks;       // workgroups of that part
+  PtEntArgs ent;
 };
 
 // the 32 bin codes of block q of a row (the row pitch is a multiple of 32
@@ -729,17 +745,23 @@ __device__ __forceinline__ void fill_runs(const FormArgs& a, long long r, int q,
   }
 }
 
-// the first workgroups fill the runs (`group` lanes per row), the others
-// scatter (a wave per chunk)
+// the first workgroups build the tiled propagation's entries, the next fill
+// the runs (`group` lanes per row), the others scatter (a wave per chunk)
 __global__ __launch_bounds__(256) void k_fill(FormArgs a) {
-  extern __shared__ int pos[];  // [waves][B+1] running positions of the chunks
+  // [waves][B+1] running positions of the chunks, or TileEntriesLds
+  extern __shared__ __align__(16) int pos[];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if ((int)blockIdx.x >= a.rowblocks) {
-    const long long c = (long long)(blockIdx.x - a.rowblocks) * (blockDim.x >> 6) + w;
-    if (c < a.nblk) scatter_chunk(a, c, pos + w * (a.B + 1));
+  if ((int)blockIdx.x < a.entblocks) {
+    tile_entries(a.ent, (int)blockIdx.x, *reinterpret_cast<TileEntriesLds*>(pos));
     return;
   }
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int block = (int)blockIdx.x - a.entblocks;
+  if (block >= a.rowblocks) {
+    const long long c = (long long)(block - a.rowblocks) * a.swaves + w;
+    if (w < a.swaves && c < a.nblk) scatter_chunk(a, c, pos + w * (a.B + 1));
+    return;
+  }
+  const long long t = (long long)block * 256 + threadIdx.x;
   const long long r = t / a.group;
   const bool in = r < a.rows;
   const int g = lane & (a.group - 1);
@@ -820,12 +842,28 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
     if (err != hipSuccess) return err;
   }
   hipLaunchKernelGGL(k_offsets, dim3(2), dim3(1024), 0, s, m);
+  m.rowblocks = (int)((rowthreads + 255) / 256);
   // four chunks per workgroup while their positions fit in 64 KB of LDS
-  const int waves = (size_t)(mm.B + 1) * 16 <= 65536 ? 4 : 2;
-  m.rowblocks = (int)((rowthreads + 64 * waves - 1) / (64 * waves));
-  const long long blocks = m.rowblocks + (L.nblk + waves - 1) / waves;
-  hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(64 * waves),
-                     (size_t)(mm.B + 1) * 4 * waves, s, m);
+  m.swaves = (size_t)(mm.B + 1) * 16 <= 65536 ? 4 : 2;
+  size_t fill_lds = (size_t)(mm.B + 1) * 4 * m.swaves;
+  if (mm.grid.ndim == 2) {
+    const int nbx = (mm.grid.n[1] + kPX - 1) / kPX, nby = (mm.grid.n[0] + kPL - 1) / kPL;
+    m.ent.n[0] = mm.grid.n[0];
+    m.ent.n[1] = mm.grid.n[1];
+    m.ent.pitch = mm.pitch;
+    m.ent.B = mm.B;
+    m.ent.ntx = nbx;
+    m.ent.binmap = a.binmap;
+    m.ent.entries = reinterpret_cast<uint2*>(ws + L.off_tents);
+    m.ent.chunks = reinterpret_cast<PtChunk*>(ws + L.off_tchunks);
+    m.ent.blocks = reinterpret_cast<PtBlock*>(ws + L.off_tblocks);
+    m.ent.cap = mm.N / 10;
+    m.ent.counter = a.counters + kCntTiles;
+    m.entblocks = nbx * nby;
+    if (fill_lds < sizeof(TileEntriesLds)) fill_lds = sizeof(TileEntriesLds);
+  }
+  const long long blocks = m.entblocks + m.rowblocks + (L.nblk + m.swaves - 1) / m.swaves;
+  hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(256), fill_lds, s, m);
   return hipGetLastError();
 }
 

@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "vup_device.hpp"
 #include "vup_internal.hpp"
@@ -1023,73 +1024,106 @@ __device__ __forceinline__ void prop_runs(const SweepArgs& a, float* smem, int r
 // eight the 64-VGPR budget spilled a few per-thread addresses of the finish,
 // and their scratch writes doubled the kernel's HBM write traffic (138 MB per
 // launch at grid1024 against the 67 MB of P) for no gain in time
-template <int RR>
-__global__ __launch_bounds__(kThreads, 7) void k_propagate_runs(SweepArgs a) {
-  extern __shared__ float smem[];
-  if (!runs_chosen(a)) return;  // k_propagate does the work
-  const long long k = block_k(a);
-  if (k >= a.d.K) return;
-  const int D = a.g.ndim;
-  double* red = reinterpret_cast<double*>(smem + a.L.red_off);
-  RunScales* ps = reinterpret_cast<RunScales*>(red + 16);
-  const uint32_t* hist = reinterpret_cast<const uint32_t*>(smem + a.L.hist_off);
-  float* Pk = a.P + k * (long long)a.B;
-  bool anybad = false;
-  bool written = false;
-  for (int c = 0; c < a.d.C; ++c) {
-    const long long kc = k * a.d.C + c;
-    const Win w = make_win(a, kc, reinterpret_cast<int*>(smem + a.L.red_off + 80));
-    if (w.bad) {
-      anybad = true;
-      if (a.Z && threadIdx.x == 0) a.Z[kc] = __builtin_nan("");
-      continue;
-    }
-    if (w.empty) {
-      if (a.Z && threadIdx.x == 0) a.Z[kc] = 0.0;
-      continue;
-    }
-    int loL, WL;
-    last_axis(w, D, loL, WL);
-    __syncthreads();  // LDS reuse across components
-    // factor tables of the slower axes
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      if (d + 1 < D) {
-        float* tab = smem + a.L.tab_off[d];
-        const double mu = a.d.mu[kc * D + d], rsig = 1.0 / a.d.sigma[kc * D + d];
-        const double off = scale_log(win_m(a, smem, d));
-        for (int i = threadIdx.x; i < w.W[d]; i += kThreads)
-          tab[i] = gauss_factor_r(cell_centre(a.g.lo[d], a.g.hi[d], a.g.n[d], w.lo[d] + i), mu,
-                                  rsig, off);
-      }
-    }
-    for (int i = threadIdx.x; i < 3 * a.L.hist_stride; i += kThreads) smem[a.L.hist_off + i] = 0.0f;
-    build_prefix_runs(a, smem, kc, loL, WL, scale_log(win_m(a, smem, D - 1)), red);
-    const double Zrows = row_mass(a, smem, w, red);
-    if (threadIdx.x == 0) {
-      const double colmass = reinterpret_cast<const double*>(smem + a.L.g_off)[loL + WL];
-      const double R = (double)w.R;
-      const double K = 4294967296.0 - 1048576.0 - R * (double)WL;
-      const double rowbound[3] = {Zrows, fmin(Zrows, R * (double)kClassT1),
-                                  fmin(Zrows, R * (double)kClassT2)};
-      for (int r = 0; r < 3; ++r) {
-        ps->srow[r] = K / (prec_qfac<VUP_FP32>() * rowbound[r] * colmass);
-        ps->unscale[r] = 1.0 / ps->srow[r];
-      }
-      ps->mexp = win_scale_exp(a, smem);
-    }
-    for (long long r0 = 0; r0 < w.R; r0 += RR) {
-      const int rc = (int)((w.R - r0) < RR ? (w.R - r0) : RR);
-      __syncthreads();
-      build_rows_runs(a, smem, w, r0, rc, ps, loL, loL + WL - 1);
-      __syncthreads();
-      prop_runs(a, smem, rc);
-    }
-    __syncthreads();
-    finish_component(a, hist, 3, 1, ps->unscale, red, kc, &ps->mexp, Pk, written);
-    written = true;
+// LIST: for the distributions of a device-side list (those the tiled form
+// leaves over; usually none), each workgroup taking every gridDim.x / 8th of
+// its XCD's share (as block_k, neighbours in the list share an XCD's L2)
+struct NoList {
+  __device__ bool next(long long&) { return false; }
+};
+struct RunList {
+  const int* list;
+  const int* count;
+  int at, end;
+  __device__ bool first(long long& k) {
+    const int n = *count, share = (n + 7) / 8, x = blockIdx.x & 7;
+    at = x * share + (int)(blockIdx.x >> 3);
+    end = min(x * share + share, n);
+    if (at < end) k = list[at];
+    return at < end;
   }
-  finish_column(a, Pk, anybad, written);
+  __device__ bool next(long long& k) {
+    at += gridDim.x / 8;
+    if (at >= end) return false;
+    k = list[at];
+    __syncthreads();  // LDS reuse
+    return true;
+  }
+};
+
+template <int RR, typename LIST>
+__global__ __launch_bounds__(kThreads, 7) void k_propagate_runs(SweepArgs a, LIST list) {
+  extern __shared__ float smem[];
+  long long k;
+  if constexpr (std::is_same_v<LIST, RunList>) {
+    if (!list.first(k)) return;
+  } else {
+    if (!runs_chosen(a)) return;  // k_propagate does the work
+    k = block_k(a);
+    if (k >= a.d.K) return;
+  }
+  do {
+    const int D = a.g.ndim;
+    double* red = reinterpret_cast<double*>(smem + a.L.red_off);
+    RunScales* ps = reinterpret_cast<RunScales*>(red + 16);
+    const uint32_t* hist = reinterpret_cast<const uint32_t*>(smem + a.L.hist_off);
+    float* Pk = a.P + k * (long long)a.B;
+    bool anybad = false;
+    bool written = false;
+    for (int c = 0; c < a.d.C; ++c) {
+      const long long kc = k * a.d.C + c;
+      const Win w = make_win(a, kc, reinterpret_cast<int*>(smem + a.L.red_off + 80));
+      if (w.bad) {
+        anybad = true;
+        if (a.Z && threadIdx.x == 0) a.Z[kc] = __builtin_nan("");
+        continue;
+      }
+      if (w.empty) {
+        if (a.Z && threadIdx.x == 0) a.Z[kc] = 0.0;
+        continue;
+      }
+      int loL, WL;
+      last_axis(w, D, loL, WL);
+      __syncthreads();  // LDS reuse across components
+      // factor tables of the slower axes
+  #pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (d + 1 < D) {
+          float* tab = smem + a.L.tab_off[d];
+          const double mu = a.d.mu[kc * D + d], rsig = 1.0 / a.d.sigma[kc * D + d];
+          const double off = scale_log(win_m(a, smem, d));
+          for (int i = threadIdx.x; i < w.W[d]; i += kThreads)
+            tab[i] = gauss_factor_r(cell_centre(a.g.lo[d], a.g.hi[d], a.g.n[d], w.lo[d] + i), mu,
+                                    rsig, off);
+        }
+      }
+      for (int i = threadIdx.x; i < 3 * a.L.hist_stride; i += kThreads) smem[a.L.hist_off + i] = 0.0f;
+      build_prefix_runs(a, smem, kc, loL, WL, scale_log(win_m(a, smem, D - 1)), red);
+      const double Zrows = row_mass(a, smem, w, red);
+      if (threadIdx.x == 0) {
+        const double colmass = reinterpret_cast<const double*>(smem + a.L.g_off)[loL + WL];
+        const double R = (double)w.R;
+        const double K = 4294967296.0 - 1048576.0 - R * (double)WL;
+        const double rowbound[3] = {Zrows, fmin(Zrows, R * (double)kClassT1),
+                                    fmin(Zrows, R * (double)kClassT2)};
+        for (int r = 0; r < 3; ++r) {
+          ps->srow[r] = K / (prec_qfac<VUP_FP32>() * rowbound[r] * colmass);
+          ps->unscale[r] = 1.0 / ps->srow[r];
+        }
+        ps->mexp = win_scale_exp(a, smem);
+      }
+      for (long long r0 = 0; r0 < w.R; r0 += RR) {
+        const int rc = (int)((w.R - r0) < RR ? (w.R - r0) : RR);
+        __syncthreads();
+        build_rows_runs(a, smem, w, r0, rc, ps, loL, loL + WL - 1);
+        __syncthreads();
+        prop_runs(a, smem, rc);
+      }
+      __syncthreads();
+      finish_component(a, hist, 3, 1, ps->unscale, red, kc, &ps->mexp, Pk, written);
+      written = true;
+    }
+    finish_column(a, Pk, anybad, written);
+  } while (list.next(k));
 }
 
 // ===========================================================================
@@ -2011,10 +2045,12 @@ hipError_t launch_propagate(const vup_mm& mm, const vup_dists& d, int prec, floa
     const long long nwg = 8 * ((d.K + 7) / 8);
     if (nwg <= 2048 && sweep_layout(mm.grid, mm.B, kSweepRuns, &ar.L, 2 * kRunRowChunk) &&
         ar.L.bytes <= 64 * 1024) {
-      hipLaunchKernelGGL(k_propagate_runs<2 * kRunRowChunk>, grid, block, ar.L.bytes, s, ar);
+      hipLaunchKernelGGL((k_propagate_runs<2 * kRunRowChunk, NoList>), grid, block, ar.L.bytes, s,
+                         ar, NoList{});
     } else {
       sweep_layout(mm.grid, mm.B, kSweepRuns, &ar.L);
-      hipLaunchKernelGGL(k_propagate_runs<kRunRowChunk>, grid, block, ar.L.bytes, s, ar);
+      hipLaunchKernelGGL((k_propagate_runs<kRunRowChunk, NoList>), grid, block, ar.L.bytes, s, ar,
+                         NoList{});
     }
     e = hipGetLastError();
     if (e != hipSuccess || mm.sweep == VUP_SWEEP_RUNS) return e;
@@ -2036,6 +2072,18 @@ hipError_t launch_propagate(const vup_mm& mm, const vup_dists& d, int prec, floa
       break;
     default: hipLaunchKernelGGL(k_propagate<VUP_FP32>, grid, block, a.L.bytes, s, a); break;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_propagate_list(const vup_mm& mm, const vup_dists& d, const int* klist,
+                                 const int* kcount, float* P, double* Z, hipStream_t s) {
+  SweepArgs a = base_args(mm, d, kSweepRuns);
+  a.P = P;
+  a.Z = Z;
+  // seven workgroups per CU are resident; with an empty list they end at once
+  const unsigned blocks = 1792;  // (a multiple of the 8 XCDs)
+  hipLaunchKernelGGL((k_propagate_runs<kRunRowChunk, RunList>), dim3(blocks), dim3(kThreads),
+                     a.L.bytes, s, a, RunList{klist, kcount, 0, 0});
   return hipGetLastError();
 }
 

@@ -215,6 +215,31 @@ int vup_propagate(const vup_mm* mm, const vup_dists* d, int32_t precision, float
                   "vup_propagate");
 }
 
+size_t vup_propagate_tiled_workspace_bytes(const vup_mm* mm, const vup_dists* d,
+                                           int32_t precision) {
+  if (check_mm(mm) || check_dists(d, mm->grid.ndim)) return 0;
+  if (!vup::propagate_tiled_applies(*mm, *d, precision)) return 0;
+  return vup::propagate_tiled_ws_bytes(*mm, d->K);
+}
+
+int vup_propagate_tiled(const vup_mm* mm, const vup_dists* d, int32_t precision, void* ws,
+                        size_t ws_bytes, float* P, double* Z, void* stream) {
+  int r = check_mm(mm);
+  if (r) return r;
+  if ((r = check_dists(d, mm->grid.ndim))) return r;
+  if (!vup::propagate_tiled_applies(*mm, *d, precision))
+    return vup_propagate(mm, d, precision, P, Z, stream);
+  if (!P) return fail(VUP_EINVAL, "P is NULL");
+  if ((r = check_sweep(mm, vup::kSweepPropagate))) return r;
+  const size_t need = vup::propagate_tiled_ws_bytes(*mm, d->K);
+  if (!ws) return fail(VUP_EWORKSPACE, "workspace is NULL");
+  if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(VUP_EWORKSPACE, "workspace not 256-byte aligned");
+  if (ws_bytes < need) return fail(VUP_EWORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, need);
+  if ((r = check_device())) return r;
+  return launched(vup::launch_propagate_tiled(*mm, *d, ws, P, Z, (hipStream_t)stream),
+                  "vup_propagate_tiled");
+}
+
 size_t vup_separable_workspace_bytes(const vup_mm* mm, int32_t Mx, int32_t My) {
   if (check_mm(mm) || mm->grid.ndim != 2 || Mx < 1 || My < 1) return 0;
   return vup::sep_workspace_bytes(mm->grid, mm->B, Mx, My);
@@ -344,6 +369,10 @@ int vup_set_sweep_mode(vup_mm* mm, int32_t mode, void* stream) {
     if (e != hipSuccess) return launched(e, "vup_set_sweep_mode");
     const int64_t nruns = cnt[vup::kCntRuns];
     const bool runs = vup::runs_allowed(*mm) && nruns > 0 && nruns * vup::kRunMinLength <= mm->N;
+    mm->reserved = mm->grid.ndim == 2 && vup::tiles_pay((unsigned long long)cnt[vup::kCntTiles],
+                                                        (unsigned long long)nruns)
+                       ? vup::kTilesPay
+                       : vup::kTilesNot;
     mode = runs ? VUP_SWEEP_RUNS : VUP_SWEEP_CELLS;
     // the device follows the same rule while no form was forced on it
     if (cnt[vup::kCntMode] == VUP_SWEEP_AUTO) {

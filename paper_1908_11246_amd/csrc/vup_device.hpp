@@ -30,7 +30,8 @@ constexpr int kMaxBinsPerThread = (VUP_MAX_BINS + 1 + kThreads - 1) / kThreads;
 // [4]: number of runs of equal bin along the fastest axis (set by vup_bin,
 // not cleared by vup_counters); the propagation uses the run form when the
 // mean run length is at least kRunMinLength cells.
-// [5]: scratch of the run construction; [6]: sweep mode (VUP_SWEEP_*).
+// [5]: scratch of the run construction; [6]: sweep mode (VUP_SWEEP_*); [7]:
+// entries of the tiled propagation (2-D grids, set by vup_bin).
 enum Counter {
   kCntOutside = 0,
   kCntBadEdges = 1,
@@ -38,9 +39,16 @@ enum Counter {
   kCntEmpty = 3,
   kCntRuns = 4,
   kCntScratch = 5,
-  kCntMode = 6
+  kCntMode = 6,
+  kCntTiles = 7
 };
 constexpr int kRunMinLength = 3;
+// the tiled propagation pays for a model matrix of so many entries (of four
+// row steps each; a count past its room is far larger) and runs: a row step
+// costs about a third of a run of the per-pdf kernel
+__host__ __device__ inline bool tiles_pay(unsigned long long entries, unsigned long long nruns) {
+  return entries < (1ull << 40) && 4 * entries <= 3 * nruns;
+}
 
 // grid + bin-map description passed by value to every sweep kernel
 struct GridDev {

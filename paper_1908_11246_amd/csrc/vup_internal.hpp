@@ -51,6 +51,27 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
 hipError_t launch_windows(const vup_grid& g, const vup_dists& d, int32_t* win, hipStream_t s);
 hipError_t launch_propagate(const vup_mm& mm, const vup_dists& d, int prec, float* P, double* Z,
                             hipStream_t s);
+// FP32 propagation of many single-component pdfs on a 2-D grid by tiles, one
+// pdf per lane (model matrices in the run form). From 16 384 pdfs on it was
+// faster than the per-pdf kernel at every size and deviation measured (sin/cos
+// model, deviations 0.05-0.5 and 0.05-0.1: 256^2 cells 110 -> 62 and 75 -> 52
+// us, 512^2 150 -> 74 and 83 -> 48, 1024^2 with 256 bins 375 -> 181 and 111 ->
+// 99); at 8100 pdfs narrow ones on 1024^2 cells take 76 us instead of 60, the
+// time of a few batches one after the other.
+constexpr long long kPtMinK = 16384;
+// vup_mm.reserved once vup_set_sweep_mode(AUTO) has looked: the tiled
+// propagation pays for the model matrix, or not (0: not looked, the device
+// decides on each call)
+constexpr int kTilesPay = 1, kTilesNot = 2;
+// bytes of the tiled propagation's entries of a 2-D model matrix
+void tile_entry_sizes(const vup_grid& g, size_t* ents, size_t* chunks, size_t* blocks);
+bool propagate_tiled_applies(const vup_mm& mm, const vup_dists& d, int prec);
+size_t propagate_tiled_ws_bytes(const vup_mm& mm, long long K);
+hipError_t launch_propagate_tiled(const vup_mm& mm, const vup_dists& d, void* ws, float* P,
+                                  double* Z, hipStream_t s);
+// the run form for the *kcount distributions klist[0 .. *kcount) (device)
+hipError_t launch_propagate_list(const vup_mm& mm, const vup_dists& d, const int* klist,
+                                 const int* kcount, float* P, double* Z, hipStream_t s);
 hipError_t launch_moments(const vup_mm& mm, const vup_dists& d, const vup_model* model,
                           double* mean, double* var, double* delta2, hipStream_t s);
 // moments by tiles of the model values on the matrix cores (2-D grids,
@@ -79,7 +100,8 @@ struct WsLayout {
   int64_t nblk;  // chunks of the bin sort
   int chunk;     // padded positions per chunk
   size_t off_edges, off_binmap, off_f32, off_counts, off_offsets, off_perm, off_scratch,
-      off_counters, off_runs, off_rowptr, off_runidx, off_tsum, bytes;
+      off_counters, off_runs, off_rowptr, off_runidx, off_tsum, off_tents, off_tchunks, off_tblocks,
+      bytes;
 };
 bool ws_layout(const vup_grid& g, int B, WsLayout* out);
 // exclusive prefix sum of n ints in place; tsum: scan_tiles(n) int64 scratch;

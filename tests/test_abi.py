@@ -351,3 +351,50 @@ def test_separable_arguments(lib):
     mm3 = _fake_mm(lib, n=(4, 4))
     mm3.grid = _grid((4, 4, 4), (0, 0, 0), (1, 1, 1))
     assert sep(ctypes.byref(mm3), ctypes.byref(s), ws, need, dummy, None, None) == EUNSUPPORTED
+
+
+def test_propagate_tiled_validation(lib):
+    """vup_propagate_tiled: where it applies, its workspace, and vup_propagate's
+    rules elsewhere."""
+    mm = _fake_mm(lib, n=(256, 256))
+    dummy, ws = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x200000)
+
+    def dists(**kw):
+        d = vup.VupDists()
+        d.K, d.ncomp, d.ndim, d.n_sigma = 16384, 1, 2, 4.0
+        d.mu, d.sigma, d.weight = 0x1000, 0x2000, None
+        for k, v in kw.items():
+            setattr(d, k, v)
+        return d
+
+    def need(d, prec=0, m=mm):
+        return lib.vup_propagate_tiled_workspace_bytes(ctypes.byref(m), ctypes.byref(d), prec)
+
+    def call(d, w, nb, P=dummy, prec=0):
+        return lib.vup_propagate_tiled(ctypes.byref(mm), ctypes.byref(d), prec, w, nb, P, None,
+                                       None)
+
+    # unresolved or per-cell sweep form: not tiled
+    assert need(dists()) == 0
+    mm.sweep = 1
+    assert need(dists()) == 0
+    mm.sweep = 2
+    nb = need(dists())
+    # 88 bytes per pdf; 8 tiles of one list: 32 KiB of positions, 1 KiB of batches
+    assert 16384 * 88 + 8 * 33 * 1024 <= nb <= 16384 * 88 + 8 * 33 * 1024 + 4096
+    assert need(dists(K=16383)) == 0 and need(dists(K=1 << 24)) == 0
+    assert need(dists(), prec=1) == 0 and need(dists(ncomp=2, weight=0x3000)) == 0
+    mm.reserved = 2  # found not to pay
+    assert need(dists()) == 0
+    mm.reserved = 1
+    assert need(dists()) == nb
+    big = _fake_mm(lib, n=(256, 256), B=4096)
+    big.sweep = 2
+    assert need(dists(K=1 << 17), m=big) > 0 and need(dists(K=1 << 18), m=big) == 0
+    assert call(dists(), None, nb) == EWORKSPACE
+    assert call(dists(), ctypes.c_void_p(0x200010), nb) == EWORKSPACE
+    assert call(dists(), ws, nb - 1) == EWORKSPACE
+    assert call(dists(), ws, nb, P=None) == EINVAL
+    assert call(dists(K=-1), ws, nb) == EINVAL
+    assert call(dists(K=5), None, 0, P=None) == EINVAL
+    assert call(dists(), ws, nb, prec=9) == EINVAL

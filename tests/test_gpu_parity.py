@@ -20,6 +20,7 @@ Bars (per distribution k unless noted):
 The oracle always computes its own f, edges and bins; when a kernel is tested
 in isolation, the GPU is fed the oracle's inputs (never the other way round).
 """
+import ctypes
 import math
 import sys
 import zlib
@@ -1199,3 +1200,74 @@ def test_step_graph_capture(vup):
         torch.cuda.synchronize()
         _say(f"  replay {i}: " + ", ".join(str(torch.equal(a, b)) for a, b in zip(outs, ref)))
         assert all(torch.equal(a, b) for a, b in zip(outs, ref)), i
+
+
+# ---------------------------------------------------------------------------
+# propagation by tiles (many pdfs, one per lane)
+# ---------------------------------------------------------------------------
+# The tiled form forms its column factors to 2^-27 of the Gaussian's peak, its
+# row factors in FP64 and its sums in integers of 2^-32 of the pdf's mass (at
+# most one rounding per bin, four rows and tile), so a column's L1 error stays
+# far below the FP32 bar of 2e-5; cells without a bin take their mass out of
+# the column, so the sums are compared with the oracle's.
+TILED = [
+    # name, grid, lo, hi, model, bins, edges as a share of f's range, sigma range in cells
+    ("one_tile", (64, 64), (-3.0, -3.0), (3.0, 3.0), "sincos2", 24, 1.0, (1.0, 12.0)),
+    ("ragged_edges", (129, 65), (-3.0, -3.0), (3.0, 3.0), "sincos2", 16, 1.0, (0.3, 30.0)),
+    ("short_rows", (700, 40), (-3.0, -1.0), (3.0, 1.0), "sincos2", 20, 1.0, (2.0, 20.0)),
+    ("long_rows", (33, 400), (-3.0, -3.0), (3.0, 3.0), "sincos2", 60, 1.0, (1.0, 40.0)),
+    ("cells_without_bin", (190, 150), (-3.0, -3.0), (3.0, 3.0), "sincos2", 20, 0.6, (1.0, 15.0)),
+    ("two_passes", (256, 512), (-3.0, -3.0), (3.0, 3.0), "sincos2", 160, 1.0, (2.0, 30.0)),
+    ("one_bin", (100, 90), (-3.0, -3.0), (3.0, 3.0), "sincos2", 1, 1.0, (1.0, 10.0)),
+    ("steep_rows", (300, 260), (-5.0, -1.0), (5.0, 1.0), "ipsa2", 300, 1.0, (2.0, 12.0)),
+    ("short_runs", (96, 96), (-3.0, -3.0), (3.0, 3.0), "timing2", 900, 1.0, (1.0, 8.0)),
+]
+
+
+@pytest.mark.parametrize("resolve", [True, False], ids=["auto", "forced"])
+@pytest.mark.parametrize("case", TILED, ids=[c[0] for c in TILED])
+def test_propagate_tiled(vup, orc, case, resolve):
+    """Every column against the oracle, the form chosen at set-up or on the
+    device: means in and outside the grid, deviations from a third of a cell
+    to the grid's size, invalid pdfs and empty windows among them, in no order."""
+    name, n, lo, hi, model, B, share, srange = case
+    K = 16384 + 77
+    rng = np.random.Generator(np.random.PCG64(zlib.crc32(name.encode())))
+    lo_, hi_ = np.asarray(lo), np.asarray(hi)
+    h = (hi_ - lo_) / np.asarray(n)
+    mu = rng.uniform(lo_ - 3 * h, hi_ + 3 * h, size=(K, 1, 2))
+    sg = np.exp(rng.uniform(np.log(srange[0]), np.log(srange[1]), size=(K, 1, 2))) * h
+    sg[5, 0, 0], sg[77, 0, 1], mu[300, 0, 0] = 0.0, np.nan, np.inf
+    mu[1000:1010] = hi_ + 100.0
+    _say(f"[propagate tiled {name} {'auto' if resolve else 'forced'}] n={n} B={B} K={K}")
+    f = orc.eval_grid(n, lo, hi, model)
+    c, r = 0.5 * (f.min() + f.max()), 0.5 * (f.max() - f.min()) * share
+    e = np.linspace(c - r, c + r, B + 1)
+    if share == 1.0:
+        e = orc.uniform_edges(f, B)
+    b = orc.bins(f, e)
+    Po, Zo = orc.propagate(n, lo, hi, b, B, mu, sg)
+    g = vup.make_grid(n, lo, hi)
+    mm = vup.build_model_matrix(g, torch.from_numpy(f).to(DEV), torch.from_numpy(e).to(DEV),
+                                resolve_sweep=resolve)
+    if not resolve or name == "short_runs":
+        mm.set_sweep_mode("runs")
+    d = vup._dists(torch.empty((K, 1, 2), device=DEV), torch.empty((K, 1, 2), device=DEV), None,
+                   4.0)
+    nb = vup.lib().vup_propagate_tiled_workspace_bytes(ctypes.byref(mm.mm), ctypes.byref(d), 0)
+    _say(f"  sweep {mm.sweep}, tiled workspace {nb} bytes")
+    if not resolve:
+        assert nb > 0
+    mm.counters()
+    P, Z = vup.propagate(mm, mu, sg)
+    cnt = mm.counters()
+    Pg, zg = _cpu(P).astype(np.float64), _cpu(Z)[:, 0]
+    bad = ~np.isfinite(Po).all(axis=1)
+    assert np.isnan(Pg[bad]).all() and np.isfinite(Pg[~bad]).all() and bad.sum() == 3
+    assert cnt["bad_param"] == 3 and cnt["empty"] == int((Zo[:, 0] == 0).sum())
+    l1 = np.abs(Pg - Po)[~bad].sum(axis=1)
+    rz = np.abs(zg - Zo[:, 0])[~bad] / np.maximum(Zo[~bad, 0], 1e-300)
+    _say(f"  max L1 {l1.max():.3e} (bar 2e-5), Z max rel err {rz.max():.2e} (bar 2e-6)")
+    assert l1.max() <= 2e-5 and rz.max() <= 2e-6
+    P2, _ = vup.propagate(mm, mu, sg)
+    assert torch.equal(P.nan_to_num(-1.0), P2.nan_to_num(-1.0))
