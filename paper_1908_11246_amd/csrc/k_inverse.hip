@@ -8,13 +8,22 @@
 // its power of two 2^m) and their product; the mixture weight, 2^-sum m,
 // 1/Z_{k,c} and 1/P_b are combined in FP64 per bin and applied in FP32.
 //   k_posterior       workgroups over grid rows: per-bin factors
-//                     pi_c / (Z_c P_b), the fastest-axis factors and the
-//                     row's factor product staged, one multiply-add per cell
+//                     pi_c / (Z_c P_b) in LDS, the rows' factor products and
+//                     the columns' factors staged, one multiply-add per cell
 //                     and component
-//   k_posterior_mean  E[x_d | y in b, k] = sum over the bin's cells of
-//                     post x_d, one wave per (t, b) walking the part of the
-//                     model matrix's compressed-by-bin cell list inside the
-//                     window's index range (fixed summation order)
+//   k_posterior_mean_tab  E[x_d | y in b, k] = sum over the bin's cells of
+//                     post x_d, over the part of the model matrix's
+//                     compressed-by-bin cell list inside the window's index
+//                     range (fixed summation order)
+//   k_posterior_mean  the same for grids whose factor tables do not fit, one
+//                     wave per (t, b), reading post
+//
+// 64 of 256 locations, 1000^2 cells, 1000 bins: k_posterior writes 256 MB in
+// 40 us (82 us with a row's factors computed by every thread and one row in
+// flight), the means 57 us (133 us reading post; 93 us from tables with a wave
+// per bin, where the searches and wave sums of 64 000 bins of 300 cells cost
+// more than the cells). Copies reach 5.1 TB/s, so k_posterior is bound by its
+// stores; the means by their LDS gathers and the walk's instructions.
 #include <hip/hip_runtime.h>
 
 #include "vup_device.hpp"
@@ -46,7 +55,6 @@ struct PostArgs {
   float* post;
   double* mean;
   int gtab;                 // the fastest-axis factor table fits in LDS
-  int vec;                  // rows of post take float4 stores (n_L % 4 == 0, aligned)
   double rn[4];             // 1 / n_d, for the index arithmetic of the means
 };
 
@@ -55,8 +63,10 @@ struct PostArgs {
 // factor f[c][b] = pi_c / (Z_c P[k][b]) of every bin (0 where P is 0), so a
 // cell costs its fastest-axis factor and one multiply-add per component.
 // Per row: the product of the other axes' factors (uniform over the row).
+constexpr int kPostRows = 64;  // rows whose factors are kept at once
+template <bool VEC>
 __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
-  extern __shared__ float sfb[];  // [C][B], then (when it fits) the fastest-axis factors [C][n_L]
+  extern __shared__ float sfb[];  // [C][B + 1], then (!VEC, when it fits) fastest-axis factors [C][n_L]
   __shared__ int swin[VUP_MAX_COMP][VUP_MAX_DIM][2];
   __shared__ double smu[VUP_MAX_COMP][VUP_MAX_DIM], srs[VUP_MAX_COMP][VUP_MAX_DIM];
   __shared__ int sm[VUP_MAX_COMP][VUP_MAX_DIM];  // the factors' scale exponents
@@ -100,14 +110,15 @@ __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
       const int c = e / B, b = e - c * B;
       const float ev = a.P[k * B + b];
       if (!isfinite(ev)) atomicOr(&sbad, 1);
-      sfb[e] = ev > 0.0f ? (float)(sfac[c] / (double)ev) : 0.0f;
+      sfb[c * (B + 1) + b] = ev > 0.0f ? (float)(sfac[c] / (double)ev) : 0.0f;
     }
   }
+  if (threadIdx.x < C) sfb[threadIdx.x * (B + 1) + B] = 0.0f;  // cells without a bin
   const int nL = a.n[D - 1];
   // the fastest-axis factor of every column inside each component's window,
   // shared by all rows of this distribution
-  float* gtab = sfb + C * B;
-  if (a.gtab && kok) {
+  float* gtab = sfb + C * (B + 1);
+  if (!VEC && a.gtab && kok) {
     // only the window's columns: the cells read no others
     for (int c = 0; c < C; ++c) {
       const int wlo = swin[c][D - 1][0], whi = swin[c][D - 1][1];
@@ -171,31 +182,98 @@ __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
                                  : gauss_factor_r(cell_centre(a.lo[D - 1], a.hi[D - 1], nL, col),
                                                   smu[c][D - 1], srs[c][D - 1],
                                                   scale_log(sm[c][D - 1]));
-          v = fmaf(ri.rf[c] * g, sfb[c * B + b], v);
+          v = fmaf(ri.rf[c] * g, sfb[c * (B + 1) + b], v);
         }
       }
     }
     return v;
   };
-  if (a.vec) {
-    // four columns per thread: one 8-byte load of bin codes, one 16-byte store
+  if constexpr (VEC) {
+    // A thread owns four columns: their fastest-axis factors stay in registers
+    // (-1 outside the component's window) while it goes down the workgroup's
+    // rows, four rows at once (four 8-byte loads of bin codes, four 16-byte
+    // stores). A row's factor products are computed once per 64 rows, one row
+    // per thread.
+    __shared__ float srow[kPostRows][VUP_MAX_COMP];
     const float fill = bad ? __builtin_nanf("") : 0.0f;
-    for (int r = blockIdx.x; r < a.rows; r += gridDim.x) {
-      RowInfo ri;
-      row_info(r, ri);
-      const uint16_t* brow = a.binmap + (long long)r * a.pitch;
-      float4* prow4 = reinterpret_cast<float4*>(post + (long long)r * nL);
-      for (int c4 = threadIdx.x; c4 < (nL >> 2); c4 += blockDim.x) {
+    const int n4 = nL >> 2;
+    int tx = 256;
+    while (tx > 4 && tx / 2 >= n4) tx >>= 1;  // threads along a row
+    const int ty = 256 / tx;
+    const int x = threadIdx.x & (tx - 1), y = threadIdx.x / tx;
+    const int stride = gridDim.x;
+    for (int rbase = blockIdx.x; rbase < a.rows; rbase += kPostRows * stride) {
+      const int nr = min(kPostRows, (int)((a.rows - rbase + stride - 1) / stride));
+      __syncthreads();
+      if ((int)threadIdx.x < nr) {
+        RowInfo ri;
+        row_info(rbase + (int)threadIdx.x * stride, ri);
+#pragma unroll
+        for (int c = 0; c < VUP_MAX_COMP; ++c)
+          srow[threadIdx.x][c] = ri.chi[c] >= ri.clo[c] ? ri.rf[c] : -1.0f;
+      }
+      __syncthreads();
+      for (int c4 = x; c4 < n4; c4 += tx) {
         const int col0 = 4 * c4;
-        float4 o = make_float4(fill, fill, fill, fill);
-        if (!bad && col0 + 3 >= ri.ulo && col0 <= ri.uhi) {
-          const uint2 cw = *reinterpret_cast<const uint2*>(brow + col0);
-          o.x = cell(ri, col0, cw.x & 0xFFFFu);
-          o.y = cell(ri, col0 + 1, cw.x >> 16);
-          o.z = cell(ri, col0 + 2, cw.y & 0xFFFFu);
-          o.w = cell(ri, col0 + 3, cw.y >> 16);
+        float g[VUP_MAX_COMP][4];
+        bool any = false;
+#pragma unroll
+        for (int c = 0; c < VUP_MAX_COMP; ++c) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            g[c][e] = -1.0f;
+            if (c < C && !bad && col0 + e >= swin[c][D - 1][0] && col0 + e <= swin[c][D - 1][1]) {
+              g[c][e] = gauss_factor_r(cell_centre(a.lo[D - 1], a.hi[D - 1], nL, col0 + e),
+                                       smu[c][D - 1], srs[c][D - 1], scale_log(sm[c][D - 1]));
+              any = true;
+            }
+          }
         }
-        prow4[c4] = o;
+        constexpr int U = 4;
+        for (int q0 = y; q0 < nr; q0 += U * ty) {
+          uint2 cw[U];
+          float rf[U][VUP_MAX_COMP];
+          bool on[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int q = min(q0 + u * ty, nr - 1);
+            on[u] = false;
+#pragma unroll
+            for (int c = 0; c < VUP_MAX_COMP; ++c) {
+              rf[u][c] = srow[q][c];
+              on[u] = on[u] || rf[u][c] >= 0.0f;
+            }
+            on[u] = on[u] && any;
+            cw[u] = make_uint2(0u, 0u);
+            if (on[u])
+              cw[u] = *reinterpret_cast<const uint2*>(
+                  a.binmap + (long long)(rbase + q * stride) * a.pitch + col0);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * ty;
+            float o[4] = {fill, fill, fill, fill};
+            if (on[u]) {
+              const uint32_t code[4] = {cw[u].x & 0xFFFFu, cw[u].x >> 16, cw[u].y & 0xFFFFu,
+                                        cw[u].y >> 16};
+#pragma unroll
+              for (int c = 0; c < VUP_MAX_COMP; ++c) {
+                if (c < C && rf[u][c] >= 0.0f) {
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) {
+                    const float fb = *reinterpret_cast<const float*>(
+                        reinterpret_cast<const char*>(sfb + c * (B + 1)) + code[e]);
+                    const float v = fmaf(rf[u][c] * g[c][e], fb, o[e]);
+                    if (g[c][e] >= 0.0f) o[e] = v;
+                  }
+                }
+              }
+            }
+            if (q < nr)
+              *reinterpret_cast<float4*>(post + (long long)(rbase + q * stride) * nL + col0) =
+                  make_float4(o[0], o[1], o[2], o[3]);
+          }
+        }
       }
     }
   } else {
@@ -257,6 +335,221 @@ __device__ __forceinline__ void wave_lower_bounds(const int* list, long long s0,
   }
   r0 = finish_search(list, a, x0, lane);
   r1 = finish_search(list, b, x1, lane);
+}
+
+// The means without reading post: a workgroup per (t, a stretch of bins) keeps
+// the factor tables of all axes in LDS and forms a cell's posterior again from
+// its factors, with k_posterior's operations in k_posterior's order
+// (bit-identical), so the cells' 4-byte gathers from post, each a 128-byte
+// line from memory for a bin one cell wide, fall away. The parts of the bins'
+// lists inside the window's index range are found first, a thread per bin and
+// end; then LPB lanes walk a bin (lane l the cells l, l + LPB, ... of its
+// part) and their sums are taken in a fixed order.
+// sum over the lane's row of 16 lanes, given to all of them
+__device__ __forceinline__ double row_last(double v) {
+  const long long b = __double_as_longlong(row_scan(v));
+  const int src = (threadIdx.x & 63) | 15;
+  const int lo = __shfl((int)(b & 0xFFFFFFFF), src, 64), hi = __shfl((int)(b >> 32), src, 64);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+struct MeanDiv {
+  uint32_t mul[4];  // j / n_d = mulhi(j, mul) >> shift for j < 2^31 (n_d > 1)
+  int shift[4];
+};
+
+template <int D, int C, int LPB>
+__global__ __launch_bounds__(256) void k_posterior_mean_tab(PostArgs a, MeanDiv dv, int per) {
+  // [C][n_0 + ... + n_(D-1)] factors, -1 outside the component's window;
+  // [2][per] ends of the bins' parts
+  extern __shared__ float tab[];
+  __shared__ int swin[C][D][2];
+  __shared__ double smu[C][D], srs[C][D];
+  __shared__ int sm[C][D];
+  __shared__ double sfac[C];
+  __shared__ int sbad;
+  const long long t = blockIdx.y;
+  const long long k = a.sel[t];
+  const bool kok = k >= 0 && k < a.K;
+  if (threadIdx.x == 0) sbad = kok ? 0 : 1;
+  __syncthreads();
+  if (threadIdx.x < C * D && kok) {
+    const int c = threadIdx.x / D, d = threadIdx.x % D;
+    const long long pidx = (k * C + c) * D + d;
+    const double mu = a.mu[pidx], sg = a.sigma[pidx];
+    int lo, hi;
+    const bool ok = axis_window(a.lo[d], a.hi[d], a.n[d], mu, sg, a.ns, lo, hi);
+    swin[c][d][0] = lo;
+    swin[c][d][1] = hi;
+    smu[c][d] = mu;
+    srs[c][d] = 1.0 / sg;
+    sm[c][d] = (ok && hi >= lo) ? axis_scale_exp(a.lo[d], a.hi[d], a.n[d], lo, hi, mu, 1.0 / sg)
+                                : 0;
+    if (!ok) atomicOr(&sbad, 1);
+  }
+  if (kok)
+    for (int e = threadIdx.x; e < a.B; e += 256)
+      if (!isfinite(a.P[k * a.B + e])) atomicOr(&sbad, 1);
+  __syncthreads();
+  if (threadIdx.x < C && kok) {
+    const int c = threadIdx.x;
+    int ms = 0;
+    for (int d = 0; d < D; ++d) ms += sm[c][d];
+    const double z = a.Z[k * C + c];
+    const double w = C > 1 ? a.weight[k * C + c] : 1.0;
+    sfac[c] = ldexp(w / z, -ms);
+    if (!isfinite(z)) atomicOr(&sbad, 1);
+  }
+  __syncthreads();
+  const bool bad = sbad != 0;
+  int blo[D], bhi[D], base[D + 1];
+  base[0] = 0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    blo[d] = 0x7fffffff;
+    bhi[d] = -1;
+    base[d + 1] = base[d] + a.n[d];
+  }
+  bool any = false;  // some component's window is not empty
+  if (!bad) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      bool cin = true;
+#pragma unroll
+      for (int d = 0; d < D; ++d) cin = cin && swin[c][d][1] >= swin[c][d][0];
+      any = any || cin;
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int lo = swin[c][d][0], hi = swin[c][d][1];
+        if (cin) {
+          blo[d] = min(blo[d], lo);
+          bhi[d] = max(bhi[d], hi);
+        }
+        const double mu = smu[c][d], rs = srs[c][d], off = scale_log(sm[c][d]);
+        for (int i = threadIdx.x; i < a.n[d]; i += 256)
+          tab[c * base[D] + base[d] + i] =
+              cin && i >= lo && i <= hi
+                  ? gauss_factor_r(cell_centre(a.lo[d], a.hi[d], a.n[d], i), mu, rs, off)
+                  : -1.0f;
+      }
+    }
+  }
+  // ends of the bins' parts: first positions with a cell >= first and > last,
+  // by three probes a step
+  int* ends = reinterpret_cast<int*>(tab + C * base[D]);
+  const int b0 = blockIdx.x * per, nb = min(per, a.B - b0);
+  if (!bad && any) {
+    long long first = 0, last = 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      first = first * a.n[d] + blo[d];
+      last = last * a.n[d] + bhi[d];
+    }
+    for (int e = threadIdx.x; e < 2 * nb; e += 256) {
+      const int b = b0 + (e >> 1);
+      const int x = (int)((e & 1) ? last + 1 : first);  // at most the number of cells
+      int lo = (int)a.offsets[b], hi = (int)a.offsets[b + 1];
+      while (lo < hi) {
+        const int q = (hi - lo) >> 2;
+        const int p0 = lo + q, p1 = lo + ((hi - lo) >> 1), p2 = hi - 1 - q;
+        const int v0 = a.perm[p0], v1 = a.perm[p1], v2 = a.perm[max(p2, p1)];
+        if (v0 >= x) hi = p0;
+        else if (v1 >= x) { lo = p0 + 1; hi = p1; }
+        else if (v2 >= x) { lo = p1 + 1; hi = max(p2, p1); }
+        else lo = max(p2, p1) + 1;
+      }
+      ends[e] = lo;
+    }
+  }
+  __syncthreads();
+  constexpr int G = 64 / LPB;  // bins of a wave
+  const int lane = threadIdx.x & 63, l = lane & (LPB - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (the bins are dealt out by the wave's number, a uniform value, and the
+  // wave is kept together at the end of each)
+  for (int g0 = w * G; g0 < nb; g0 += 4 * G) {
+    const int g = g0 + lane / LPB;
+    const int b = b0 + g;
+    const bool live = g < nb;
+    const float ev = live && kok ? a.P[k * a.B + b] : 0.0f;
+    // a bin without mass has post 0 on all its cells (k_posterior's factor is
+    // 0 there): its sums are exact zeros
+    const bool on = live && !bad && any && ev > 0.0f;
+    float fb[C];
+    int s = 0, e = 0;
+    if (on) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) fb[c] = (float)(sfac[c] / (double)ev);
+      s = ends[2 * g];
+      e = ends[2 * g + 1];
+    }
+    double S0 = 0.0, S[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) S[d] = 0.0;
+    constexpr int U = 4;  // cells per lane and step, their loads in flight together
+    for (s += l; s < e; s += LPB * U) {
+      int ci[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) ci[u] = s + LPB * u < e ? a.perm[s + LPB * u] : -1;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        int j[D];
+        uint32_t rest = ci[u] < 0 ? 0u : (uint32_t)ci[u];
+#pragma unroll
+        for (int d = D - 1; d >= 1; --d) {
+          const uint32_t quo = a.n[d] == 1 ? rest : __umulhi(rest, dv.mul[d]) >> dv.shift[d];
+          j[d] = (int)(rest - quo * (uint32_t)a.n[d]);
+          rest = quo;
+        }
+        j[0] = (int)rest;
+        float v = 0.0f;
+        bool in = false;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          // the slower axes' product, then the fastest axis' factor
+          float f = 1.0f, fac = 1.0f;
+          bool cin = ci[u] >= 0;
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            fac = tab[c * base[D] + base[d] + j[d]];
+            cin = cin && fac >= 0.0f;
+            if (d + 1 < D) f *= fac;
+          }
+          const float x = fmaf(f * fac, fb[c], v);
+          if (cin) v = x;
+          in = in || cin;
+        }
+        const double qd = in ? (double)v : 0.0;
+        S0 += qd;
+#pragma unroll
+        for (int d = 0; d < D; ++d) S[d] += qd * (double)j[d];
+      }
+    }
+    double mine = 0.0;  // lane d of a bin: component d
+    S0 = LPB == 64 ? wave_sum(S0) : row_last(S0);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const double Sd = LPB == 64 ? wave_sum(S[d]) : row_last(S[d]);
+      const double h = (a.hi[d] - a.lo[d]) / a.n[d];
+      const double md = a.lo[d] * S0 + h * (Sd + 0.5 * S0);
+      if (l == d) mine = md;
+    }
+    if (live && l < D) {
+      // NaN where the posterior row is NaN (0 for a bin without cells)
+      if (!on) mine = bad && a.offsets[b + 1] > a.offsets[b] ? __builtin_nan("") : 0.0;
+      a.mean[(t * a.B + b) * D + l] = mine;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <int D>
+static void launch_mean_tab(const PostArgs& a, const MeanDiv& dv, int per, bool narrow, dim3 grid,
+                            size_t lds, hipStream_t s) {
+  void (*kern)(PostArgs, MeanDiv, int) =
+      a.C == 1 ? (narrow ? k_posterior_mean_tab<D, 1, 16> : k_posterior_mean_tab<D, 1, 64>)
+               : (narrow ? k_posterior_mean_tab<D, 2, 16> : k_posterior_mean_tab<D, 2, 64>);
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a, dv, per);
 }
 
 // one wave per (t, b): lanes take the bin's cells lane, lane + 64, ... of the
@@ -419,20 +712,54 @@ hipError_t launch_posterior(const vup_mm& mm, const vup_dists& d, int64_t n_sel,
   a.mean = mean;
   for (int x = 0; x < 4; ++x) a.rn[x] = 1.0 / a.n[x];
   const int nL = a.n[a.ndim - 1];
-  a.gtab = (size_t)d.ncomp * (mm.B + nL) * sizeof(float) <= 65536 ? 1 : 0;
-  a.vec = (nL % 4 == 0) && ((reinterpret_cast<uintptr_t>(post) & 15u) == 0);
-  const size_t lds = (size_t)d.ncomp * (mm.B + (a.gtab ? nL : 0)) * sizeof(float);
+  const bool vec = (nL % 4 == 0) && ((reinterpret_cast<uintptr_t>(post) & 15u) == 0);
+  a.gtab = (size_t)d.ncomp * (mm.B + 1 + nL) * sizeof(float) <= 65536 ? 1 : 0;
+  const size_t lds = (size_t)d.ncomp * (mm.B + 1 + (a.gtab && !vec ? nL : 0)) * sizeof(float);
   // about 32 rows per workgroup, so the per-bin factors and the factor table
-  // are set up rarely, but at least 4096 workgroups in all while rows last
+  // are set up rarely, but at least 2048 workgroups in all while rows last
   long long gx = (mm.rows + 31) / 32;
-  const long long want = (4096 + n_sel - 1) / n_sel;
+  const long long want = (2048 + n_sel - 1) / n_sel;
   if (gx < want) gx = want < mm.rows ? want : mm.rows;
   gx = gx < 1 ? 1 : (gx > 4096 ? 4096 : gx);
-  hipLaunchKernelGGL(k_posterior, dim3((unsigned)gx, (unsigned)n_sel), dim3(256), lds, s, a);
+  const dim3 grid((unsigned)gx, (unsigned)n_sel);
+  if (vec) hipLaunchKernelGGL(k_posterior<true>, grid, dim3(256), lds, s, a);
+  else hipLaunchKernelGGL(k_posterior<false>, grid, dim3(256), lds, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !mean) return e;
-  hipLaunchKernelGGL(k_posterior_mean, dim3((unsigned)((mm.B + 3) / 4), (unsigned)n_sel),
-                     dim3(256), 0, s, a);
+  size_t tab = 0;
+  for (int x = 0; x < a.ndim; ++x) tab += (size_t)a.n[x];
+  tab *= d.ncomp * sizeof(float);
+  // tables up to 32 KB leave four workgroups to a CU (64 locations, 1000^2
+  // cells: 57 us, 133 us without tables)
+  if (tab <= 32768) {
+    // bins per workgroup: about 2048 workgroups, each with a few bins per wave
+    // to share its tables
+    // a quarter of a wave per bin fills the chip from 16 384 bins on (same
+    // size: 57 us, 93 us with a wave per bin); fewer bins take a wave each
+    const bool narrow = n_sel * mm.B >= 16384;
+    long long per = (n_sel * mm.B + 2047) / 2048;
+    if (per < 16) per = 16;
+    if (per > 256) per = 256;
+    MeanDiv dv{};
+    for (int x = 0; x < a.ndim; ++x) {
+      int l = 0;
+      while ((1ll << l) < a.n[x]) ++l;
+      // ceil(2^(31 + l) / n) < 2^32, exact for dividends below 2^31
+      if (l > 0) {
+        dv.mul[x] = (uint32_t)(((1ull << (31 + l)) + a.n[x] - 1) / a.n[x]);
+        dv.shift[x] = l - 1;
+      }
+    }
+    const dim3 mgrid((unsigned)((mm.B + per - 1) / per), (unsigned)n_sel);
+    const size_t mlds = tab + 2 * (size_t)per * sizeof(int);
+    if (a.ndim == 1) launch_mean_tab<1>(a, dv, (int)per, narrow, mgrid, mlds, s);
+    else if (a.ndim == 2) launch_mean_tab<2>(a, dv, (int)per, narrow, mgrid, mlds, s);
+    else if (a.ndim == 3) launch_mean_tab<3>(a, dv, (int)per, narrow, mgrid, mlds, s);
+    else launch_mean_tab<4>(a, dv, (int)per, narrow, mgrid, mlds, s);
+  } else {
+    hipLaunchKernelGGL(k_posterior_mean, dim3((unsigned)((mm.B + 3) / 4), (unsigned)n_sel),
+                       dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -176,6 +176,51 @@ def test_posterior_long_fastest_axis(vup, orc):
     _run(vup, orc, wl, [0, 5, 11], "long axis")
 
 
+@pytest.mark.parametrize("n,B,C,n_sel", [
+    ((37,), 5, 1, 3),            # one axis
+    ((64, 260), 300, 1, 60),     # sixteen lanes per bin
+    ((64, 260), 300, 2, 12),     # a wave per bin
+    ((5, 1, 12), 7, 2, 4),       # an axis of one cell, a row of three float4
+    ((7, 6, 5, 8), 90, 1, 200),
+    ((7, 6, 5, 9), 41, 2, 9),
+    ((3, 9000), 50, 1, 5),       # factor tables past the LDS: means read post
+])
+def test_posterior_means_are_sums_of_post(vup, n, B, C, n_sel):
+    """The means are sums over the posterior that the same call returns, with
+    nothing in between but FP64 rounding: of a sum of m terms at most about m
+    2^-53 of the sum of their magnitudes, and a few units for x_d (lo + (j +
+    1/2) h) and the way the sum is split, so 2 (m + 8) 2^-53 of it."""
+    d = len(n)
+    rng = np.random.default_rng(B)
+    g = vup.make_grid(n, (-1.0,) * d, (1.5,) * d)
+    f = torch.from_numpy(rng.normal(size=int(np.prod(n)))).to(DEV)
+    mm = vup.build_model_matrix(g, f, vup.uniform_edges(f, B))
+    K = n_sel + 3
+    mu = rng.uniform(-1.2, 1.7, size=(K, C, d))  # some windows past the domain
+    sigma = rng.uniform(0.1, 0.5, size=(K, C, d))
+    w = rng.dirichlet(np.ones(C), size=K) if C > 1 else None
+    P, Z = vup.propagate(mm, mu, sigma, w)
+    P[1, B // 2] = 0.0           # a bin without mass
+    P[2, 0] = float("nan")       # an invalid row
+    sel = np.r_[rng.permutation(K)[:n_sel - 2], 2, K]  # and an index out of range
+    post, mean = vup.posterior(mm, mu, sigma, w, sel, P, Z)
+    post, mean = _cpu(post).astype(np.float64), _cpu(mean)
+    b = _cpu(mm.bin)
+    x = np.meshgrid(*[-1.0 + (np.arange(m) + 0.5) * (2.5 / m) for m in n], indexing="ij")
+    x = np.stack([v.ravel() for v in x], axis=1)
+    counts = np.bincount(b, minlength=B)
+    for t in range(n_sel):
+        if np.isnan(post[t]).any():
+            assert np.isnan(post[t]).all()
+            assert np.array_equal(np.isnan(mean[t]), np.repeat(counts[:, None] > 0, d, axis=1))
+            continue
+        for i in range(d):
+            want = np.bincount(b, weights=post[t] * x[:, i], minlength=B)
+            size = np.bincount(b, weights=post[t] * 2.5, minlength=B)
+            assert np.all(np.abs(mean[t, :, i] - want) <= 2 * (counts + 8) * 2.0 ** -53 * size), t
+    assert np.isnan(post[-2]).all() and np.isnan(post[-1]).all()
+
+
 def test_timing_study_workload_small_L(vup, orc):
     """The Sec. 4.1 timing workload (N = 10^6, untruncated pdfs over the
     whole grid) at L = 3 against the oracle: the configuration bench.py times
