@@ -15,6 +15,11 @@
 // The column kernels give one wave64 to one column at a time (see
 // stream_columns); the bin edges sit once per workgroup in LDS. All HBM
 // traffic is one read of P and one write of the outputs.
+//
+// 65 536 columns of 256 bins, 512 target cells, five levels: matrix 46 us (96
+// with a bin corrected against the edges for every point; its 201 MB take 39 us
+// at the 5.1 TB/s of a copy), field lines 26 us (48 us with ballots per level
+// and round for the quantiles; 67 MB, so the FP64 sums and scans bound it).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -107,21 +112,11 @@ __device__ __forceinline__ void stream_columns(const float* __restrict__ P, long
   }
 }
 
-__device__ __forceinline__ double shfl_f64(double v, int src) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __shfl((int)(b & 0xFFFFFFFF), src, 64);
-  const int hi = __shfl((int)(b >> 32), src, 64);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// value of the previous lane of the group (0 for the group's first lane)
+// value of the previous lane of the group (0 for the group's first lane):
+// DPP row_shr:1 or wave_shr:1
 template <int LPC>
 __device__ __forceinline__ double grp_prev(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __shfl_up((int)(b & 0xFFFFFFFF), 1, LPC);
-  const int hi = __shfl_up((int)(b >> 32), 1, LPC);
-  const double p = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-  return (threadIdx.x & (LPC - 1)) == 0 ? 0.0 : p;
+  return dpp_f64<LPC == 16 ? 0x111 : 0x138>(v);
 }
 
 // inclusive scan within the group
@@ -134,7 +129,7 @@ __device__ __forceinline__ double grp_scan(double v) {
 // the group's last lane's value, given to every lane of the group
 template <int LPC>
 __device__ __forceinline__ double grp_last(double v) {
-  if constexpr (LPC == 16) return shfl_f64(v, (threadIdx.x & 63) | 15);
+  if constexpr (LPC == 16) return dpp_f64<0x15F>(v);  // row_newbcast:15
   else return lane_value(v, 63);
 }
 
@@ -317,9 +312,17 @@ __device__ __forceinline__ int count_le_from(const double* E, int B, double t, i
 // The matrix gives a column a whole wave. The J + 1 grid points d_j + y are
 // taken round-robin (lane l of round r has point 64 r + l), so the lanes of a
 // round look up adjacent bins (no LDS bank conflicts); Q_j = F(j+1) - F(j)
-// comes from the neighbouring lane. With near-uniform edges (each within half
-// an average bin width of its uniform position) a point's bin is guessed
-// arithmetically and corrected exactly; otherwise it is found by bisection.
+// comes from the neighbouring lane.
+//
+// With edges uniform to within their own rounding (those of vup_uniform_edges)
+// a point's position in bins is u_j = j (h / w) + (d_lo + y - e_0) / w, its bin
+// and the fraction of it the integer and fractional part of u_j: eleven FP64
+// operations, one 16-byte LDS read and no comparison with an edge. The bin
+// edges differ from their uniform positions by less than the rounding of d_j +
+// y, which this form does not have. Its rounds go down from the last point, so
+// that a round's 64 cells are one aligned store. With near-uniform edges (each
+// within half an average bin width) a point's bin is guessed arithmetically and
+// corrected exactly; otherwise it is found by bisection.
 template <int LPC, int MV, bool VEC>
 __global__ __launch_bounds__(256) void k_ipsa_matrix(MatrixArgs a) {
   // launched with LPC = 64 only (one column per wave); the launch table
@@ -329,22 +332,33 @@ __global__ __launch_bounds__(256) void k_ipsa_matrix(MatrixArgs a) {
   } else {
   constexpr int G = 1;
   extern __shared__ double lds[];
-  __shared__ int s_nonuniform;
+  __shared__ int s_near, s_exact;
   const int B = a.B;
   double* E = lds;
   double* invw = lds + (B + 1);
   const int lane = threadIdx.x & 63;
   const int r = lane & (LPC - 1);
   const int g = lane / LPC;
-  double* C = lds + (2 * B + 1) + ((threadIdx.x >> 6) * G + g) * (B + 1);
-  if (threadIdx.x == 0) s_nonuniform = 0;
+  double* C = lds + (2 * B + 1) + ((threadIdx.x >> 6) * G + g) * (B + 2);
+  if (threadIdx.x == 0) s_near = s_exact = 1;
   stage_tables(a.edges, B, E, nullptr, invw);
   // near-uniform edges?
   const double e0 = E[0], wbar = (E[B] - E[0]) / B;
-  for (int b = threadIdx.x; b <= B; b += blockDim.x)
-    if (!(fabs(E[b] - (e0 + b * wbar)) <= 0.5 * wbar)) atomicOr(&s_nonuniform, 1);
+  // (and uniform to within rounding, with bins far wider than that)
+  const double ulps = 8.0 * 0x1p-53 * fmax(fabs(e0), fabs(E[B]));
+  double far = 0.0;  // largest distance from the uniform positions
+  bool num = true;
+#pragma unroll 1
+  for (int b = threadIdx.x; b <= B; b += blockDim.x) {
+    const double off = fabs(E[b] - (e0 + b * wbar));
+    far = fmax(far, off);
+    num = num && off == off;
+  }
+  if (!(num && far <= 0.5 * wbar)) s_near = 0;  // (any thread's store says the same)
+  if (!(num && far <= ulps && ulps <= 0x1p-36 * wbar)) s_exact = 0;
   __syncthreads();
-  const bool uniform = s_nonuniform == 0;
+  const bool uniform = __builtin_amdgcn_readfirstlane(s_near) != 0;
+  const bool exact = __builtin_amdgcn_readfirstlane(s_exact) != 0;
   const double scale = 1.0 / wbar;
   stream_columns<LPC, MV, VEC>(a.P, a.K, B, [&](long long k, bool live, const float4 (&v)[MV]) {
     double incl[MV];
@@ -361,13 +375,47 @@ __global__ __launch_bounds__(256) void k_ipsa_matrix(MatrixArgs a) {
           if (b + j < B) C[b + j] = c[j];
       }
     }
-    if (r == 0) C[B] = T;
+    if (r == 0) {
+      C[B] = T;
+      C[B + 1] = T;
+    }
     wave_lds_sync();
     float* q = a.Q + k * (long long)a.J;
     const bool fin = isfinite(T);
     if (live && !fin) {
       for (int j = lane; j < a.J; j += 64) q[j] = __builtin_nanf("");
       if (lane == 0 && a.lost) a.lost[k] = __builtin_nan("");
+    } else if (live && exact) {
+      const double y = a.y_ref[k];
+      const int J = a.J;
+      const double hs = a.dy_width * scale, u0 = ((a.dy_lo + y) - e0) * scale, Bd = (double)B;
+      auto F_at = [&](double jd) {
+        const double u = fmin(fmax(fma(jd, hs, u0), 0.0), Bd);  // (0 for NaN, as count_le)
+        const double* c = C + (int)u;
+        const double c0 = c[0], c1 = c[1];
+        return fma(c1 - c0, __builtin_amdgcn_fract(u), c0);
+      };
+      const int jtop = (J >> 6) << 6;  // the round of point J
+      double jd = (double)(jtop + lane);
+      double next = F_at(jd);  // at lane 0 of the round last done
+      const double F_end = lane_value(next, J - jtop);
+      const double Fn0 = dpp_f64<0x130>(next);  // wave_shl:1
+      if (jtop + lane < J) q[jtop + lane] = (float)(Fn0 - next);
+      next = lane_value(next, 0);
+      for (int j0 = jtop - 64; j0 >= 0; j0 -= 64) {
+        jd -= 64.0;
+        const double F = F_at(jd);
+        // the next lane's value; the last lane keeps the round before's first
+        const long long fb = __double_as_longlong(F), nb = __double_as_longlong(next);
+        const int lo = __builtin_amdgcn_update_dpp((int)(nb & 0xFFFFFFFF), (int)(fb & 0xFFFFFFFF),
+                                                   0x130, 0xF, 0xF, false);
+        const int hi = __builtin_amdgcn_update_dpp((int)(nb >> 32), (int)(fb >> 32), 0x130, 0xF,
+                                                   0xF, false);
+        const double Fn = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+        q[j0 + lane] = (float)(Fn - F);
+        next = lane_value(F, 0);
+      }
+      if (lane == 0 && a.lost) a.lost[k] = next + (T - F_end);
     } else if (live) {
       const double y = a.y_ref[k];
       const int J = a.J;
@@ -428,6 +476,8 @@ __global__ __launch_bounds__(256) void k_ipsa_fields(FieldArgs a) {
   const int lane = threadIdx.x & 63;
   const int r = lane & (LPC - 1);
   const int g = lane / LPC;
+  // 16 lanes per column: the CDF after every fourth bin, of each group's column
+  double* C4 = lev + kMaxLevels + (threadIdx.x / LPC) * (MV * LPC);
   const double nan = __builtin_nan("");
   if (threadIdx.x < kMaxLevels) lev[threadIdx.x] = a.level[threadIdx.x];
   stage_tables(a.edges, B, E, cen, nullptr);
@@ -462,7 +512,9 @@ __global__ __launch_bounds__(256) void k_ipsa_fields(FieldArgs a) {
             s2 += pt * t;
           }
         }
-        if (a.quant) {
+        if (LPC == 16) {
+          C4[LPC * i + r] = c[4];
+        } else if (a.quant) {
 #pragma unroll 1
           for (int q = 0; q < a.nq; ++q) {
             {
@@ -502,6 +554,49 @@ __global__ __launch_bounds__(256) void k_ipsa_fields(FieldArgs a) {
         }
       }
     }
+    if (LPC == 16 && a.quant) {
+      // Lane q answers level q: bisection for the four bins whose end is the
+      // first to reach it, then the bin among them. All levels of the wave's
+      // four columns take one pass of log2(B / 4) LDS reads, instead of a
+      // ballot per level and round and a branch nearly every time. (Columns of
+      // more than 1024 bins have a whole wave, and keep the ballots: their
+      // rounds are few for the bins they cover.)
+      wave_lds_sync();
+      if (live && r < a.nq) {
+        const double target = lev[r] * T;
+        double y_q = nan;
+        if (positive && target > 0.0 && target <= T) {
+          int lo = 0, hi = (B + 3) / 4 - 1;  // answer in [lo, hi]: C4[hi] >= target
+          while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (C4[mid] >= target) hi = mid;
+            else lo = mid + 1;
+          }
+          const int b = 4 * lo;
+          float p[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) p[j] = b + j < B ? a.P[k * (long long)B + b + j] : 0.0f;
+          const double c0 = lo > 0 ? C4[lo - 1] : 0.0, c1 = c0 + (double)p[0],
+                       c2 = c1 + (double)p[1], c3 = c2 + (double)p[2];
+          const int jj = c1 >= target ? 0 : c2 >= target ? 1 : c3 >= target ? 2 : 3;
+          const double cj = jj == 0 ? c0 : jj == 1 ? c1 : jj == 2 ? c2 : c3;
+          const float pb = jj == 0 ? p[0] : jj == 1 ? p[1] : jj == 2 ? p[2] : p[3];
+          if (pb > 0.0f) {
+            const double frac = fmin(fmax((target - cj) / (double)pb, 0.0), 1.0);
+            y_q = E[b + jj] + frac * (E[b + jj + 1] - E[b + jj]);
+          } else {
+            // as below: the right edge of the last positive bin before it
+            int jb = -1;
+#pragma unroll
+            for (int t2 = 0; t2 < 4; ++t2)
+              if (t2 <= jj && p[t2] > 0.0f) jb = t2;
+            y_q = jb >= 0 ? E[b + jb + 1] : E[b];
+          }
+        }
+        a.quant[k * (long long)a.nq + r] = y_q;
+      }
+      wave_lds_sync();  // C4 is rewritten for the next column
+    }
     // first maximum over the group: larger value wins, equal values keep the lower bin
     for (int o = LPC / 2; o >= 1; o >>= 1) {
       const float ov = __shfl_xor(vmax, o, 64);
@@ -518,7 +613,7 @@ __global__ __launch_bounds__(256) void k_ipsa_fields(FieldArgs a) {
       if (a.y_mode) a.y_mode[k] = positive ? cen[imax] : nan;
       if (a.dev) a.dev[k] = finite ? S1 : nan;
       if (a.delta2) a.delta2[k] = finite ? 0.5 * S2 : nan;
-      if (a.quant)
+      if (LPC != 16 && a.quant)
         for (int q = 0; q < a.nq; ++q)
           if (!(found & (1u << q))) a.quant[k * (long long)a.nq + q] = nan;
     }
@@ -618,7 +713,7 @@ hipError_t launch_ipsa_matrix(const double* edges, int B, int64_t K, const float
   a.Q = Q;
   a.lost = lost;
   const size_t fixed = (size_t)(2 * B + 1) * sizeof(double);
-  const size_t per_wave = (size_t)(64 / lpc) * (B + 1) * sizeof(double);
+  const size_t per_wave = (size_t)(64 / lpc) * (B + 2) * sizeof(double);
   const int waves = col_waves(fixed, per_wave);
   return launch_k_ipsa_matrix(a, lpc, B % 4 == 0 && aligned16(P), waves, fixed + per_wave * waves,
                               s);
@@ -642,8 +737,10 @@ hipError_t launch_ipsa_fields(const double* edges, int B, int64_t K, const float
   a.quant = quant;
   a.dev = dev;
   a.delta2 = delta2;
-  const size_t bytes = (size_t)(2 * B + 1 + kMaxLevels) * sizeof(double);
-  return launch_k_ipsa_fields(a, col_lpc(B), B % 4 == 0 && aligned16(P), 4, bytes, s);
+  const int lpc = col_lpc(B);
+  const size_t c4 = lpc == 16 ? (size_t)4 * 4 * 16 * col_rounds(B, lpc) : 0;
+  const size_t bytes = ((size_t)(2 * B + 1 + kMaxLevels) + c4) * sizeof(double);
+  return launch_k_ipsa_fields(a, lpc, B % 4 == 0 && aligned16(P), 4, bytes, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -687,16 +784,28 @@ __global__ __launch_bounds__(256) void k_marg_partial(const float* __restrict__ 
   part[(long long)blockIdx.y * n + j] = acc;
 }
 
-// out[j] = sum over chunks of part[chunk][j]: one wave per column, lanes take
-// chunks lane, lane + 64, ... and the wave sum fixes the order
-__global__ __launch_bounds__(64) void k_marg_combine(const double* __restrict__ part, int chunks,
-                                                     int n, double* __restrict__ out) {
-  const int j = blockIdx.x;
+// out[j] = sum over chunks of part[chunk][j], in a fixed order: a workgroup
+// takes 16 columns (128-byte pieces of the partial sums' rows), its thread
+// (x, y) column x of chunks y, y + 32, ..., eight loads in flight; then the 32
+// sums of a column are added in order. A wave per column with a chunk per lane
+// read 8 bytes of each line (7.6 us at 1024 chunks of 512 columns, 3.9 us so).
+__global__ __launch_bounds__(512) void k_marg_combine(const double* __restrict__ part, int chunks,
+                                                      int n, double* __restrict__ out) {
+  __shared__ double sums[32][17];
+  const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+  const int j = blockIdx.x * 16 + x;
   double s = 0.0;
+  if (j < n) {
 #pragma unroll 8
-  for (int c = threadIdx.x; c < chunks; c += 64) s += part[(long long)c * n + j];
-  s = wave_sum(s);
-  if (threadIdx.x == 0) out[j] = s;
+    for (int c = y; c < chunks; c += 32) s += part[(long long)c * n + j];
+  }
+  sums[y][x] = s;
+  __syncthreads();
+  if (y == 0 && j < n) {
+    double t = 0.0;
+    for (int q = 0; q < 32; ++q) t += sums[q][x];
+    out[j] = t;
+  }
 }
 
 hipError_t launch_marginalize(int64_t K, int n, const float* A, const double* rho, void* ws,
@@ -712,7 +821,8 @@ hipError_t launch_marginalize(int64_t K, int n, const float* A, const double* rh
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_marg_combine, dim3((unsigned)n), dim3(64), 0, s, part, chunks, n, out);
+  hipLaunchKernelGGL(k_marg_combine, dim3((unsigned)((n + 15) / 16)), dim3(512), 0, s, part,
+                     chunks, n, out);
   return hipGetLastError();
 }
 

@@ -244,6 +244,32 @@ def test_matrix_fields_bin_count_extremes(vup, orc, B):
     _check_fields(out, ofields.ipsa_fields(P32, e, y, lv), P32, e, f"fields B={B}")
 
 
+@pytest.mark.parametrize("shift", [0.0, 1e3, 1e8])
+@pytest.mark.parametrize("B,n_dy", [(1, 64), (5, 63), (61, 65), (256, 128), (1000, 1)])
+def test_matrix_fields_uniform_edges(vup, orc, B, n_dy, shift):
+    """Edges of uniform_edges: positions in bins without a comparison, where
+    the edges' rounding is far below a bin (at a shift of 1e8 it is not);
+    rounds of 64 target cells and one cell either side; all sixteen levels."""
+    rng = np.random.Generator(np.random.PCG64(B))
+    K = 37
+    e = orc.uniform_edges(shift + np.array([-1.0, 0.3, 1.7]), B)
+    P32 = (rng.random((K, B)) * (rng.random((K, B)) < 0.3)).astype(np.float32)
+    P32[4, :] = 0.0
+    P32[4, B // 2] = 1.0
+    y = rng.uniform(e[0], e[-1], size=K)
+    y[9], y[10], y[11] = np.inf, -np.inf, np.nan
+    mm = _mm_from_edges(vup, e)
+    Pt = torch.from_numpy(P32).to(DEV)
+    dy_lo, dy_w = -2.0, 4.0 / n_dy
+    Qg, lg = vup.ipsa_matrix(mm, Pt, torch.from_numpy(y).to(DEV), dy_lo, dy_w, n_dy)
+    Qo, lo_ = ofields.ipsa_matrix(P32, e, y, dy_lo, dy_w, n_dy)
+    _check_matrix(_cpu(Qg), _cpu(lg), Qo, lo_, P32, f"B={B} shift={shift}", e, y, dy_lo, dy_w)
+    lv = (1.0,) + tuple(np.linspace(0.01, 0.99, 15))
+    yfin = np.where(np.isfinite(y), y, 0.0)
+    out = vup.ipsa_fields(mm, Pt, torch.from_numpy(yfin).to(DEV), lv)
+    _check_fields(out, ofields.ipsa_fields(P32, e, yfin, lv), P32, e, f"fields B={B}")
+
+
 # ---------------------------------------------------------------------------
 # marginal over locations
 # ---------------------------------------------------------------------------
