@@ -156,11 +156,11 @@ __device__ __forceinline__ int choose_sw(int loL, int WL, long long R, int maxsw
   int best = 4;
   long long bestc = 0x7fffffffffffffffll;
   for (int sw = 4; sw <= maxsw; sw *= 2) {
-    const int ns = (loL + WL - 1) / sw - loL / sw + 1;
-    const int cols = ns < kThreads ? ns : kThreads;
-    const int P0 = kThreads / cols;
-    const long long ncg = (ns + kThreads - 1) / kThreads;
-    const long long c = ((R + P0 - 1) / P0) * ncg * (sw + 3);
+    // (32-bit divisions: window rows number below 2^31)
+    const unsigned ns = (unsigned)(loL + WL - 1) / sw - (unsigned)loL / sw + 1;
+    const unsigned P0 = ns < kThreads ? kThreads / ns : 1;
+    const unsigned ncg = (ns + kThreads - 1) / kThreads;
+    const long long c = (long long)(((unsigned)R + P0 - 1) / P0) * (ncg * (sw + 3));
     if (c < bestc) {
       bestc = c;
       best = sw;
@@ -520,14 +520,15 @@ struct RowIt {
   int i[3];
 };
 
-__device__ __forceinline__ void rowit_init(RowIt& it, long long r, const Win& w, int D) {
+__device__ __forceinline__ void rowit_init(RowIt& it, unsigned r, const Win& w, int D) {
 #pragma unroll
   for (int d = 2; d >= 0; --d) {
     it.i[d] = 0;
     if (d <= D - 2) {
       if (d > 0) {
-        it.i[d] = (int)(r % w.W[d]);
-        r /= w.W[d];
+        const unsigned q = r / (unsigned)w.W[d];
+        it.i[d] = (int)(r - q * (unsigned)w.W[d]);
+        r = q;
       } else {
         it.i[d] = (int)r;
       }
@@ -538,19 +539,7 @@ __device__ __forceinline__ void rowit_init(RowIt& it, long long r, const Win& w,
 // digits of the step kThreads (uniform)
 __device__ __forceinline__ RowIt rowit_step_digits(const Win& w, int D) {
   RowIt s;
-  long long r = kThreads;
-#pragma unroll
-  for (int d = 2; d >= 0; --d) {
-    s.i[d] = 0;
-    if (d <= D - 2) {
-      if (d > 0) {
-        s.i[d] = (int)(r % w.W[d]);
-        r /= w.W[d];
-      } else {
-        s.i[d] = (int)r;
-      }
-    }
-  }
+  rowit_init(s, kThreads, w, D);
   return s;
 }
 
@@ -683,15 +672,23 @@ __device__ __forceinline__ void prop_rows(const SweepArgs& a, float* smem, int r
 // word b nc + c), normalise by the sum over all slots (cells without a bin
 // included) and add the weighted column into Pk. The reported normaliser is
 // the mass of the densities: the tables' mass times 2^-*mexp.
-__device__ __forceinline__ void finish_cells(const SweepArgs& a, const uint32_t* hist, int nc,
+__device__ __forceinline__ void finish_cells(const SweepArgs& a, uint32_t* hist, int nc,
                                              const double* unscale, double* red, long long kc,
                                              const int* mexp, float* Pk, bool written) {
   const int B = a.B;
+  // Neighbouring lanes read different 16-byte pieces of their bins (bin b's
+  // words start 4 nc bytes apart), so that a read covers all banks. With the
+  // values of more than 512 bins kept instead of formed twice, and 512 bins
+  // and the cells without one in a single pass, 32 768 pdfs of 128^3 cells and
+  // 512 bins take 1.06 ms instead of 1.11, 8192 mixtures of 48^4 cells and 1024
+  // bins 0.89 instead of 0.91.
+  const int rot = (int)(threadIdx.x & 63) >> (6 - a.L.cshift);
   auto slot = [&](int b) {
     double v = 0.0;
     const uint32_t* h = hist + (size_t)b * nc;
     if (nc >= 4) {
-      for (int c = 0; c < nc; c += 4) {
+      for (int i = 0; i < nc / 4; ++i) {
+        const int c = 4 * ((i + rot) & (nc / 4 - 1));
         const uint4 q = *reinterpret_cast<const uint4*>(h + c);
         v += (double)q.x * unscale[c] + (double)q.y * unscale[c + 1] +
              (double)q.z * unscale[c + 2] + (double)q.w * unscale[c + 3];
@@ -702,25 +699,36 @@ __device__ __forceinline__ void finish_cells(const SweepArgs& a, const uint32_t*
     return v;
   };
   const double wk = (a.d.C > 1) ? a.d.weight[kc] : 1.0;
-  if (B + 1 <= 2 * kThreads) {
+  if (B <= 2 * kThreads) {
+    // at most two bins per thread, kept in registers, and the cells without a
+    // bin
     const int b0 = threadIdx.x, b1 = threadIdx.x + kThreads;
-    const double v0 = b0 <= B ? slot(b0) : 0.0;
-    const double v1 = b1 <= B ? slot(b1) : 0.0;
-    const double Zc = block_sum(v0 + v1, red);
+    const double v0 = b0 < B ? slot(b0) : 0.0;
+    const double v1 = b1 < B ? slot(b1) : 0.0;
+    double vn = 0.0;
+    if (threadIdx.x == kThreads - 1) vn = slot(B);
+    const double Zc = block_sum((v0 + v1) + vn, red);
     if (a.Z && threadIdx.x == 0) a.Z[kc] = ldexp(Zc, -*mexp);
     const double f = wk / Zc;
     if (b0 < B) Pk[b0] = (float)((written ? (double)Pk[b0] : 0.0) + v0 * f);
     if (b1 < B) Pk[b1] = (float)((written ? (double)Pk[b1] : 0.0) + v1 * f);
     return;
   }
+  // more bins: a bin's value takes the place of its first two words (a thread
+  // reads no bins but its own)
   double zpart = 0.0;
-  for (int b = threadIdx.x; b <= B; b += kThreads) zpart += slot(b);
+  for (int b = threadIdx.x; b <= B; b += kThreads) {
+    const double v = slot(b);
+    if (nc >= 2) *reinterpret_cast<double*>(hist + (size_t)b * nc) = v;
+    zpart += v;
+  }
   const double Zc = block_sum(zpart, red);
   if (a.Z && threadIdx.x == 0) a.Z[kc] = ldexp(Zc, -*mexp);
   const double f = wk / Zc;
   for (int b = threadIdx.x; b < B; b += kThreads) {
     const double prev = written ? (double)Pk[b] : 0.0;
-    Pk[b] = (float)(prev + slot(b) * f);
+    const double v = nc >= 2 ? *reinterpret_cast<const double*>(hist + (size_t)b * nc) : slot(b);
+    Pk[b] = (float)(prev + v * f);
   }
 }
 
@@ -791,7 +799,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_propagate(SweepArgs a) {
   const int nc = a.L.cpw;
   double* red = reinterpret_cast<double*>(smem + a.L.red_off);
   PropScales* ps = reinterpret_cast<PropScales*>(smem + a.L.red_off + 96);
-  const uint32_t* hist = reinterpret_cast<const uint32_t*>(smem + a.L.hist_off);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(smem + a.L.hist_off);
   float* Pk = a.P + k * (long long)a.B;
   bool anybad = false;
   bool written = false;  // row k holds a partial mixture

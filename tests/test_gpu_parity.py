@@ -1133,6 +1133,25 @@ def test_run_and_cell_forms_agree(vup, orc):
         assert np.array_equal(_cpu(Pu), out[mm.sweep])
 
 
+@pytest.mark.parametrize("B", [1, 255, 511, 512, 513, 1100, 4096])
+def test_cell_form_bin_counts(vup, orc, B):
+    """The cell form's finish at the bins two per thread hold, one fewer and
+    one more, and with 16, 8 and 2 copies of the histogram; a tenth of the
+    cells have no bin."""
+    wl = workloads.random_workload("finish", (23, 19, 30), (-2.0,) * 3, (2.0,) * 3, "damped3", B,
+                                   9, 2, (0.1, 0.9), seed=B)
+    f = orc.eval_grid(wl.n, wl.lo, wl.hi, wl.model)
+    e = orc.uniform_edges(np.sort(f)[f.size // 20:-f.size // 20], B)
+    Po, Zo = orc.propagate(wl.n, wl.lo, wl.hi, orc.bins(f, e), B, wl.mu, wl.sigma, wl.weight)
+    g = vup.make_grid(wl.n, wl.lo, wl.hi)
+    mm = vup.build_model_matrix(g, torch.from_numpy(f).to(DEV), torch.from_numpy(e).to(DEV))
+    mm.set_sweep_mode("cells")
+    P, Z = vup.propagate(mm, wl.mu, wl.sigma, wl.weight)
+    # (columns sum to less than 1: the cells without a bin are normalised too)
+    assert np.abs(_cpu(P).astype(np.float64) - Po).sum(axis=1).max() <= 2e-5
+    np.testing.assert_allclose(_cpu(Z), Zo, rtol=2e-5)
+
+
 def test_model_copy_is_anchored(vup):
     """The FP32 model copy inside the model matrix holds, per row, f at every
     eighth column and the FP64 difference f - f(anchor), rounded once, at the
