@@ -62,7 +62,8 @@ MOMENTS_FLOPS_PER_UPDATE = 4
 MOMENTS_INT8_MACS_PER_UPDATE = 34
 MFMA_FP64_PEAK_TFLOPS = 78.6   # MI355X dense FP64 matrix peak
 MFMA_INT8_PEAK_TOPS = 5000.0   # MI355X dense int8 matrix peak
-KERNELS = {"propagate": "k_propagate_runs (run form) / k_propagate<FP32> (cell form)",
+KERNELS = {"propagate": "k_pt_prep + k_pt_scan + k_pt_main + k_pt_final (tiles, from 16384 pdfs on) / "
+                        "k_propagate_runs (run form) / k_propagate<FP32> (cell form)",
            "moments": "k_mt_tiles + k_mt_prep + k_mt_main (v_mfma_i32_16x16x64_i8 digit "
                       "products) + k_mt_final"}
 
@@ -84,7 +85,8 @@ def traffic_bytes(kernel):
 
 # sources each measured kernel is built from (its launch and its input layout)
 KERNEL_SOURCES = {
-    "propagate": ("k_sweep.hip", "k_grid.hip", "vup_device.hpp", "vup_internal.hpp"),
+    "propagate": ("k_ptiles.hip", "k_ptiles.hpp", "k_sweep.hip", "k_grid.hip", "vup_device.hpp",
+                  "vup_internal.hpp"),
     "moments": ("k_mtiles.hip", "k_grid.hip", "vup_device.hpp", "vup_internal.hpp"),
     "ipsa": ("k_fields.hip", "vup_fields.hpp", "vup_device.hpp"),
 }
@@ -95,8 +97,10 @@ def source_sha256(kernel="propagate"):
     import hashlib
     h = hashlib.sha256()
     for name in KERNEL_SOURCES[kernel]:
-        with open(os.path.join(ROOT, "paper_1908_11246_amd", "csrc", name), "rb") as fh:
-            h.update(fh.read())
+        path = os.path.join(ROOT, "paper_1908_11246_amd", "csrc", name)
+        if os.path.exists(path):
+            with open(path, "rb") as fh:
+                h.update(fh.read())
     return h.hexdigest()
 
 
@@ -151,11 +155,11 @@ PRECISIONS = {"grid1024": ("fp32", "bf16", "bf16x2", "fp8e4m3"),
 
 CALIB_BYTES = 256 << 20
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
-# LDS rates of the run loop's operations, per CU and clock, at the vendor
-# clock: integer atomic adds to random addresses (measured on this part with a
-# microbenchmark: 6.4 lanes per clock per CU) and the LDS bandwidth (128 bytes
-# per clock per CU)
-LDS_ATOMIC_PEAK = 6.4 * 256 * 2.4e9
+# LDS rates of the tiled propagation's operations, per CU and clock, at the
+# vendor clock: integer atomic adds free of conflicts (measured on this part
+# with a microbenchmark: 15 lanes per clock per CU) and the LDS bandwidth (128
+# bytes per clock per CU)
+LDS_ATOMIC_PEAK = 15 * 256 * 2.4e9
 LDS_BYTES_PEAK = 128 * 256 * 2.4e9
 
 
@@ -501,8 +505,10 @@ def ipsa_example_runs(vup, workloads, stream, reps):
                          "sweep_form": mm.sweep, "propagate_ms": ms_prop,
                          "propagate_separable_ms": ms_sep}
     return res
-# kernel-name fragments of the sweep kernels in rocprofv3 output
-TRACE_NAMES = {"propagate": "k_propagate_runs", "moments": "k_mt_main", "ipsa": "k_ipsa<"}
+# kernel-name fragments of the sweep kernels in rocprofv3 output (the first
+# one present counts; the tiled propagation's kernels are added up)
+TRACE_NAMES = {"propagate": ("k_pt_", "k_propagate_runs"), "moments": ("k_mt_main",),
+               "ipsa": ("k_ipsa<",)}
 
 
 def _counter_rows(path):
@@ -529,10 +535,15 @@ def summarize_traffic(fetch_csv, write_csv):
         scale = CALIB_BYTES / (calib_kib * 1024.0)
         out[f"{counter.lower()}_calibration"] = {"kernel": by_dispatch[last][0][:120],
                                                  "counter_kib": calib_kib, "scale": scale}
-        for key, frag in TRACE_NAMES.items():
-            vals = [v for name, v in by_dispatch.values() if frag in name]
-            if vals:
-                per.setdefault(key, {})[counter] = vals[0] * 1024.0 * scale
+        for key, frags in TRACE_NAMES.items():
+            for frag in frags:
+                vals = {}  # each kernel's first launch
+                for name, v in by_dispatch.values():
+                    if frag in name:
+                        vals.setdefault(name, v)
+                if vals:
+                    per.setdefault(key, {})[counter] = sum(vals.values()) * 1024.0 * scale
+                    break
     for key, v in per.items():
         if "FETCH_SIZE" in v and "WRITE_SIZE" in v:
             out["kernels"][key] = {"fetch_bytes": v["FETCH_SIZE"], "write_bytes": v["WRITE_SIZE"],
@@ -552,7 +563,7 @@ def summarize_traffic(fetch_csv, write_csv):
 #   LDS conflict = SQ_LDS_BANK_CONFLICT / (256 CUs x cycles)
 #   MFMA busy    = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x cycles)
 N_XCD, N_CU, N_SIMD = 8, 256, 1024
-SWEEP_FRAGMENTS = ("k_propagate", "k_moments", "k_backward", "k_mt_main")
+SWEEP_FRAGMENTS = ("k_propagate", "k_pt_main", "k_moments", "k_backward", "k_mt_main")
 
 
 def summarize_pmc(out_path, updates, csv_paths):
@@ -729,19 +740,21 @@ def main():
                               "kernel": KERNELS["propagate"], "kernel_ms": part_ms["propagate"],
                               "ops_per_update": OPS_PER_UPDATE["propagate"]}
     if form == "runs" and len(wl.n) == 2:
-        # the run loop's own bound: per run of equal bin inside a window one
-        # random LDS atomic and two 8-byte prefix-sum reads
+        # the LDS work of the tiles: per run of equal bin inside a window one
+        # 4-byte prefix-sum read, per entry of four rows one atomic (lanes
+        # whose window covers only part of a tile, and rows an entry leaves
+        # where they are, come on top)
         win = vup.windows(g, mu, sigma)[:, 0].cpu().numpy()
         R = runs_in_windows(mm0.runidx.cpu().numpy(), int(mm0.mm.rows), int(mm0.mm.pitch), win)
         rooflines["propagate"]["lds"] = {
             "runs_per_launch": R,
-            "atomics_per_s": R / t, "atomic_peak_per_s": LDS_ATOMIC_PEAK,
-            "atomic_frac": R / t / LDS_ATOMIC_PEAK,
-            "read_bytes_per_s": 16 * R / t, "read_peak_bytes_per_s": LDS_BYTES_PEAK,
-            "read_frac": 16 * R / t / LDS_BYTES_PEAK,
-            "peaks": "random-address ds_add_u32 rate measured on this part (6.4 lanes/clk/CU) "
+            "atomics_per_s": R / 4 / t, "atomic_peak_per_s": LDS_ATOMIC_PEAK,
+            "atomic_frac": R / 4 / t / LDS_ATOMIC_PEAK,
+            "read_bytes_per_s": 4 * R / t, "read_peak_bytes_per_s": LDS_BYTES_PEAK,
+            "read_frac": 4 * R / t / LDS_BYTES_PEAK,
+            "peaks": "conflict-free ds_add_u32 rate measured on this part (15 lanes/clk/CU) "
                      "and LDS bandwidth (128 B/clk/CU), at 2.4 GHz"}
-        log(f"[bench] run loop: {R:.3e} runs, LDS atomics "
+        log(f"[bench] run sums: {R:.3e} runs, LDS atomics "
             f"{rooflines['propagate']['lds']['atomic_frac']:.2f} and prefix-sum reads "
             f"{rooflines['propagate']['lds']['read_frac']:.2f} of their peaks")
     # moments: the algorithmic flops of the two FP64-quality bilinear forms
