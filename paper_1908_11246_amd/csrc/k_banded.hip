@@ -183,14 +183,44 @@ __global__ __launch_bounds__(64) void k_sep_scatter(SepArgs a) {
   }
 }
 
+// Z[k] for k = mx M_y + my: the product of the two axes' factor sums, times
+// 2^-(m_x + m_y) to undo the columns' scaling (k_axis_factors), so that Z is
+// the mass of the truncated densities themselves
+__device__ __forceinline__ void sep_z(const SepArgs& a, long long k) {
+  const long long K = (long long)a.M[0] * a.M[1];
+  if (k >= K) return;
+  const int m[2] = {(int)(k / a.M[1]), (int)(k % a.M[1])};
+  double z = 1.0;
+  int ms = 0;
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    z *= a.Zd[d][m[d]];
+    const int jlo = a.win[d][2 * m[d]], jhi = a.win[d][2 * m[d] + 1];
+    if (jhi >= jlo)
+      ms += axis_scale_exp(a.lo[d], a.hi[d], a.n[d], jlo, jhi, a.mu[d][m[d]],
+                           1.0 / a.sigma[d][m[d]]);
+  }
+  a.Z[k] = ldexp(z, -ms);
+}
+
+__global__ __launch_bounds__(256) void k_sep_z(SepArgs a) {
+  sep_z(a, (long long)blockIdx.x * 256 + threadIdx.x);
+}
+
 // G[i][my] = sum_{iy < i} A_y[iy][my], i = 0..n_y, in FP64 from the FP32
 // factors. One workgroup per my: thread t sums a contiguous stretch of y in
 // order, an exclusive scan of the stretch totals (waves, then across waves in
 // LDS) gives each stretch its start, and the thread writes its prefix sums.
+// Workgroups past M_y form Z, 256 values each (a launch of its own took 4.6 us
+// at 65 536).
 __global__ __launch_bounds__(256) void k_axis_prefix(SepArgs a) {
   __shared__ double wtot[kWaves];
   const int my = blockIdx.x;
   const int ny = a.n[1], My = a.M[1];
+  if (my >= My) {
+    sep_z(a, (long long)(my - My) * 256 + threadIdx.x);
+    return;
+  }
   const int len = (ny + 255) / 256;
   const int i0 = threadIdx.x * len, i1 = min(ny, i0 + len);
   const float* Ay = a.A[1] + my;
@@ -355,9 +385,13 @@ __global__ __launch_bounds__(256) void k_sep_runs_tiled(SepArgs a) {
   float* mine = acc + tid;
   for (int t = 0; t < ntiles; ++t) {
     const int bt = t * kTileBins;
+    const int st = start[t], en = start[t + 1], nq = min(kTileBins, B - bt);
+    if (st == en) {  // no run of the row in these bins
+      for (int q = 0; q < nq; ++q) Tcol[(long long)(bt + q) * My] = 0.0f;
+      continue;
+    }
 #pragma unroll
     for (int q = 0; q < kTileBins; ++q) mine[q * 256] = 0.0f;
-    const int st = start[t], en = start[t + 1];
     for (int k = st; k < en; k += 8) {
       double g0[8], g1[8];
       int bb[8];
@@ -373,7 +407,6 @@ __global__ __launch_bounds__(256) void k_sep_runs_tiled(SepArgs a) {
       for (int i = 0; i < 8; ++i)
         if (bb[i] >= 0) mine[bb[i] * 256] += (float)(g1[i] - g0[i]);
     }
-    const int nq = min(kTileBins, B - bt);
     for (int q = 0; q < nq; ++q) Tcol[(long long)(bt + q) * My] = mine[q * 256];
   }
 }
@@ -758,27 +791,6 @@ __global__ __launch_bounds__(256, 4) void k_sep_gemm_bf16(SepArgs a) {
   }
 }
 
-// Z[k] for k = mx M_y + my: the product of the two axes' factor sums, times
-// 2^-(m_x + m_y) to undo the columns' scaling (k_axis_factors), so that Z is
-// the mass of the truncated densities themselves
-__global__ __launch_bounds__(256) void k_sep_z(SepArgs a) {
-  const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long K = (long long)a.M[0] * a.M[1];
-  if (k >= K) return;
-  const int m[2] = {(int)(k / a.M[1]), (int)(k % a.M[1])};
-  double z = 1.0;
-  int ms = 0;
-#pragma unroll
-  for (int d = 0; d < 2; ++d) {
-    z *= a.Zd[d][m[d]];
-    const int jlo = a.win[d][2 * m[d]], jhi = a.win[d][2 * m[d] + 1];
-    if (jhi >= jlo)
-      ms += axis_scale_exp(a.lo[d], a.hi[d], a.n[d], jlo, jhi, a.mu[d][m[d]],
-                           1.0 / a.sigma[d][m[d]]);
-  }
-  a.Z[k] = ldexp(z, -ms);
-}
-
 // per-distribution parameters of a family propagated by the general sweep:
 // mu[k][0][d], sigma[k][0][d] for k = mx M_y + my
 __global__ __launch_bounds__(256) void k_sep_expand(int Mx, int My, const double* mux,
@@ -878,15 +890,10 @@ hipError_t launch_separable(const vup_mm& mm, int Mx, int My, const double* mu_x
   hipLaunchKernelGGL(k_axis_factors, dim3(Mmax, 2), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (Z) {
-    const long long K = (long long)Mx * My;
-    hipLaunchKernelGGL(k_sep_z, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  const unsigned zblocks = Z ? (unsigned)(((long long)Mx * My + 255) / 256) : 0u;
   if (a.n[1] <= 65534) {
     // run records hold 16-bit columns: T from the runs and the y prefix sums
-    hipLaunchKernelGGL(k_axis_prefix, dim3(My), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_axis_prefix, dim3(My + zblocks), dim3(256), 0, s, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.n[1] <= kRunRowMax) {
@@ -901,6 +908,11 @@ hipError_t launch_separable(const vup_mm& mm, int Mx, int My, const double* mu_x
       hipLaunchKernelGGL(k_sep_runs, dim3(a.n[0], (My + 255) / 256), dim3(256), 0, s, a);
     }
   } else {
+    if (zblocks) {
+      hipLaunchKernelGGL(k_sep_z, dim3(zblocks), dim3(256), 0, s, a);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
     const size_t lds = (size_t)mm.B * 64 * 4;
     if (lds > 65536) {
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_sep_scatter),
