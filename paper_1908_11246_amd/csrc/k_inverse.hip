@@ -20,7 +20,7 @@
 //
 // 64 of 256 locations, 1000^2 cells, 1000 bins: k_posterior writes 256 MB in
 // 40 us (82 us with a row's factors computed by every thread and one row in
-// flight), the means 57 us (133 us reading post; 93 us from tables with a wave
+// flight), the means 49 us (133 us reading post; 93 us from tables with a wave
 // per bin, where the searches and wave sums of 64 000 bins of 300 cells cost
 // more than the cells). Copies reach 5.1 TB/s, so k_posterior is bound by its
 // stores; the means by their LDS gathers and the walk's instructions.
@@ -730,14 +730,16 @@ hipError_t launch_posterior(const vup_mm& mm, const vup_dists& d, int64_t n_sel,
   for (int x = 0; x < a.ndim; ++x) tab += (size_t)a.n[x];
   tab *= d.ncomp * sizeof(float);
   // tables up to 32 KB leave four workgroups to a CU (64 locations, 1000^2
-  // cells: 57 us, 133 us without tables)
+  // cells: 49 us, 133 us without tables)
   if (tab <= 32768) {
-    // bins per workgroup: about 2048 workgroups, each with a few bins per wave
-    // to share its tables
+    // bins per workgroup: about 4096 workgroups, but a bin for each of a
+    // workgroup's sixteen groups of lanes to share its tables (64 locations,
+    // 1000^2 cells, 1000 bins, the whole call: 16 bins 91 us, 32 bins 99, 64
+    // bins 112)
     // a quarter of a wave per bin fills the chip from 16 384 bins on (same
-    // size: 57 us, 93 us with a wave per bin); fewer bins take a wave each
+    // size: 49 us, 93 us with a wave per bin); fewer bins take a wave each
     const bool narrow = n_sel * mm.B >= 16384;
-    long long per = (n_sel * mm.B + 2047) / 2048;
+    long long per = (n_sel * mm.B + 4095) / 4096;
     if (per < 16) per = 16;
     if (per > 256) per = 256;
     MeanDiv dv{};
