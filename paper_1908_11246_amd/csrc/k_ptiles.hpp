@@ -74,7 +74,10 @@ __device__ __forceinline__ int quad_or(int v) {
 // ---------------------------------------------------------------------------
 // entries of one block of 64 x 64 cells (256 threads): a wave per rule; in
 // each, lane r walks row r, four lanes a chunk. A chunk keeps the shortest of
-// its three lists. Bound by the latency of one row's walk (about 50 steps at
+// its three lists, of equally short ones that of the first rule: lists are
+// compared by their own lengths (before they are made even), the same that a
+// wave gives up against, so that every list that could win is whole and the
+// choice does not depend on which wave comes first. Bound by the latency of one row's walk (about 50 steps at
 // 1024^2 cells and 256 bins); the workgroups of a grid of 1024^2 all run at
 // once, next to those of the scatter and the run records.
 // ---------------------------------------------------------------------------
@@ -86,7 +89,7 @@ struct TileEntriesLds {
   uint32_t cols[kPRules][kPCh][kPEnt];
   uint16_t bins[kPRules][kPCh][kPEnt];
   int count[kPRules][kPCh];
-  int best[kPCh];      // length of the shortest list so far
+  int best[kPCh];      // length of the shortest whole list so far
   int chosen[kPCh][2];  // rule, entries
   int range[kPCh][3];   // mn, mx, none
   long long base;
@@ -138,7 +141,7 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
       b = quad_min(done ? 0x7fffffff : (c << 16) | v);
       b = b == 0x7fffffff ? -1 : (b & 0xFFFF);
     }
-    // a list no shorter than one already found is given up
+    // a list that has come to the length of a whole one is longer: given up
     const bool go = b >= 0 && n < *(volatile int*)&sh.best[ch];
     if (!__any(go)) break;
     if (go) {  // uniform in the quad
@@ -163,7 +166,7 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
       sh.cols[w][ch][n] = n > 0 ? sh.cols[w][ch][n - 1] : 0u;
       sh.bins[w][ch][n] = (uint16_t)kPNoBin;
     }
-    sh.count[w][ch] = whole ? n + (n & 1) : kPEnt + 2;
+    sh.count[w][ch] = whole && n <= kPEnt ? n : kPEnt + 2;
   }
   __syncthreads();
   // the shortest list of each chunk, and room for them
@@ -171,8 +174,9 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
     int rule = 0;
     for (int t = 1; t < kPRules; ++t)
       if (sh.count[t][threadIdx.x] < sh.count[rule][threadIdx.x]) rule = t;
+    const int n_rule = sh.count[rule][threadIdx.x];
     sh.chosen[threadIdx.x][0] = rule;
-    sh.chosen[threadIdx.x][1] = sh.count[rule][threadIdx.x];
+    sh.chosen[threadIdx.x][1] = n_rule + (n_rule & 1);
   }
   __syncthreads();
   int before[kPCh + 1];  // uniform
