@@ -448,7 +448,11 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
             ent = ev[lane];
           }
           if (!any) continue;  // no pdf of the batch has these rows
-          double last = 4503599627370496.0 * ((gx[0] + gx[1]) + (gx[2] + gx[3]));  // G = 0
+          // the sum at G = 0, by add()'s operations in add()'s order: an entry
+          // that moves no row over mass then gives exactly 0
+          double last = gx[0] * 4503599627370496.0;
+#pragma unroll
+          for (int j = 1; j < kPR; ++j) last = __builtin_fma(gx[j], 4503599627370496.0, last);
           for (int f = 0; f < n; f += 64) {
             const int m = min(64, n - f);  // even
             uint2 e = first;

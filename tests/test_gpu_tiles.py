@@ -135,3 +135,39 @@ def test_tiled_result_does_not_depend_on_the_build(vup, orc):
         if first is None:
             first = P, Z
         assert torch.equal(P, first[0]) and torch.equal(Z, first[1]), i
+
+
+# ---------------------------------------------------------------------------
+# what the sums keep
+# ---------------------------------------------------------------------------
+def _gaussians(n, lo, hi, K, cells, seed):
+    rng = np.random.default_rng(seed)
+    h = (np.asarray(hi) - np.asarray(lo)) / np.asarray(n)
+    mu = rng.uniform(lo, hi, size=(K, 1, 2))
+    return mu, np.exp(rng.uniform(*np.log(cells), size=(K, 1, 2))) * h
+
+
+def _reached(vup, mm, b, mu, sg, B):
+    """[K][B]: the pdf's window has a cell of the bin (2-D prefix sums per bin)."""
+    n = (mm.grid.n[0], mm.grid.n[1])
+    w = _cpu(vup.windows(mm.grid, mu, sg))[:, 0].astype(np.int64)
+    out = np.zeros((len(w), B), dtype=bool)
+    b2 = b.reshape(n)
+    for q in range(B):
+        c = np.zeros((n[0] + 1, n[1] + 1), dtype=np.int64)
+        c[1:, 1:] = (b2 == q).cumsum(0).cumsum(1)
+        (l0, h0), (l1, h1) = (w[:, 0, 0], w[:, 0, 1] + 1), (w[:, 1, 0], w[:, 1, 1] + 1)
+        out[:, q] = c[h0, h1] - c[l0, h1] - c[h0, l1] + c[l0, l1] > 0
+    return out
+
+
+@pytest.mark.parametrize("cells", [(0.5, 1.0), (1.0, 4.0), (4.0, 40.0)])
+@pytest.mark.parametrize("n,B,share", [((256, 256), 64, 1.0), ((190, 150), 20, 0.6)])
+def test_bins_outside_the_window_are_exact_zeros(vup, orc, n, B, share, cells):
+    mm, b = _matrix(vup, orc, n, B, share=share)
+    mu, sg = _gaussians(n, LO, HI, 16384, cells, B)
+    P, _ = vup.propagate(mm, mu, sg)
+    P, reached = _cpu(P), _reached(vup, mm, b, mu, sg, B)
+    _say(f"[zeros {n} B={B} {cells}] {(~reached).sum()} bins out of reach, "
+         f"{(P[~reached] != 0).sum()} of them with mass")
+    assert (~reached).any() and (P[~reached] == 0).all()
