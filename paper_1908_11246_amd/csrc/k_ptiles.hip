@@ -142,6 +142,9 @@ __device__ __forceinline__ double mass_bound(double lo, double h, int jlo, int j
   const double rs = 0.7071067811865476 / sigma;
   const float ta = (float)((lo + (jlo + 0.5) * h - mu) * rs);
   const float tb = (float)((lo + (jhi + 0.5) * h - mu) * rs);
+  // (a pdf so wide that its factors differ by less than the bound's margin: the
+  // cells themselves; further out ta and tb would lose their digits)
+  if (!(tb - ta > 1e-4f)) return (double)(jhi - jlo + 1);
   const double area = 1.2533141373155003 * sigma / h * (double)(erff(tb) - erff(ta));
   return area * (1.0 + 1e-5) + 1.0;
 }

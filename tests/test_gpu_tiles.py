@@ -171,3 +171,21 @@ def test_bins_outside_the_window_are_exact_zeros(vup, orc, n, B, share, cells):
     _say(f"[zeros {n} B={B} {cells}] {(~reached).sum()} bins out of reach, "
          f"{(P[~reached] != 0).sum()} of them with mass")
     assert (~reached).any() and (P[~reached] == 0).all()
+
+
+def test_very_wide_pdfs(vup, orc):
+    """Deviations up to the largest double: flat over the grid, Z the number of
+    cells, P the share of each bin."""
+    n, B, K = (131, 200), 40, 16384
+    mm, b = _matrix(vup, orc, n, B)
+    rng = np.random.default_rng(5)
+    mu = rng.uniform(-3, 3, size=(K, 1, 2))
+    sg = 10.0 ** rng.uniform(8, 308, size=(K, 1, 2))
+    sg[:8, 0] = [[1e20, 1e20], [1e39, 1.0], [1.0, 1e45], [1e50, 1e50], [1e150, 1e300], [1e307, 1e307],
+                 [1.7e308, 1.7e308], [2.0, 1e307]]
+    P, Z = vup.propagate(mm, mu, sg)
+    P, Z = _cpu(P).astype(np.float64), _cpu(Z)[:, 0]
+    Po, Zo = orc.propagate(n, LO, HI, b, B, mu, sg)
+    # FP32 output of sums with far more bits: the bar of the FP32 columns
+    assert np.isfinite(P).all() and np.abs(P - Po).sum(1).max() <= 2e-5
+    np.testing.assert_allclose(Z, Zo[:, 0], rtol=2e-6)
