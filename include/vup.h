@@ -221,25 +221,31 @@ int vup_propagate(const vup_mm* mm, const vup_dists* d, int32_t precision, float
 /* --------------------------------------------------------------------------
  * vup_propagate_tiled - vup_propagate (same arguments, outputs and NaN / zero
  * rules) with a device workspace, which lets large sets of pdfs share the
- * model matrix: the pdfs whose windows meet a tile of 64 x 64 cells are swept
+ * model matrix: the pdfs whose windows meet a tile of 128 x 64 cells are swept
  * together, one per lane, over the tile's runs of equal bin. Results agree
- * with vup_propagate's up to rounding and are bit-identical from run to run.
+ * with vup_propagate's up to rounding (with more digits in bins of little mass)
+ * and are bit-identical from run to run.
  * Applies to FP32 densities of single-component pdfs (ncomp == 1), K in
  * [16384, 2^24) and K B < 2^30, on 2-D grids of fewer than 2^28 cells and at
  * most 65 536 blocks of 64 x 64 cells whose sweep form is VUP_SWEEP_RUNS, with
- * at most 2^27 / 16384 tiles of 128 x 64 cells per 16384 pdfs (the lists of
- * the pdfs that meet each tile), unless VUP_SWEEP_AUTO found the model
- * matrix's rows too unlike each other to share; other calls are
- * vup_propagate's and ignore ws. Invalid pdfs, empty windows, means outside
- * the grid and deviations below half a cell are handed to vup_propagate's
- * kernel on the device.
- *   ws: dev, 256-byte aligned, ws_bytes >= the size below (88 bytes per pdf
- *   and 33 KB per tile and 16384 pdfs; 0 when the tiled form does not apply;
- *   then ws may be NULL). EWORKSPACE: workspace missing, unaligned or too
- *   small.
+ * at most 2^27 / 16384 tiles per 16384 pdfs (the lists of the pdfs that meet
+ * each tile), unless VUP_SWEEP_AUTO found the model matrix's rows too unlike
+ * each other to share; other calls are vup_propagate's and ignore ws. Invalid
+ * pdfs, empty windows and densities at the end of FP64's range (below e^-700
+ * in every cell) are handed to vup_propagate's kernel on the device.
+ *   ws: dev, 256-byte aligned, ws_bytes >= the first size below (88 bytes per
+ *   pdf and 33 KB per tile and 16384 pdfs; 0 when the tiled form does not
+ *   apply; then ws may be NULL). EWORKSPACE: workspace missing, unaligned or
+ *   too small.
+ *   The sums take 8 (B + 1) bytes per pdf more. With the second, full size all
+ *   pdfs are swept at once, or in shares whose sums are about 256 MB; with less
+ *   in more and smaller shares; and where they would fall below 16384 pdfs,
+ *   vup_propagate's kernel takes the call.
  * ------------------------------------------------------------------------ */
 size_t vup_propagate_tiled_workspace_bytes(const vup_mm* mm, const vup_dists* d,
                                            int32_t precision);
+size_t vup_propagate_tiled_full_workspace_bytes(const vup_mm* mm, const vup_dists* d,
+                                                int32_t precision);
 int vup_propagate_tiled(const vup_mm* mm, const vup_dists* d, int32_t precision, void* ws,
                         size_t ws_bytes, float* P, double* Z, void* stream);
 

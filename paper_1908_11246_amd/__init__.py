@@ -102,6 +102,9 @@ def _load():
     lib.vup_propagate.argtypes = [_P(VupMM), _P(VupDists), ctypes.c_int32, _vp, _vp, _vp]
     lib.vup_propagate_tiled_workspace_bytes.restype = ctypes.c_size_t
     lib.vup_propagate_tiled_workspace_bytes.argtypes = [_P(VupMM), _P(VupDists), ctypes.c_int32]
+    lib.vup_propagate_tiled_full_workspace_bytes.restype = ctypes.c_size_t
+    lib.vup_propagate_tiled_full_workspace_bytes.argtypes = \
+        lib.vup_propagate_tiled_workspace_bytes.argtypes
     lib.vup_propagate_tiled.argtypes = [_P(VupMM), _P(VupDists), ctypes.c_int32, _vp,
                                         ctypes.c_size_t, _vp, _vp, _vp]
     lib.vup_moments.argtypes = [_P(VupMM), _P(VupDists), _P(VupModel), _vp, _vp, _vp, _vp]
@@ -333,7 +336,7 @@ def propagate(mm: ModelMatrix, mu, sigma, weight=None, precision: str = "fp32",
     lib = _load()
     mref, dref, prec = ctypes.byref(mm.mm), ctypes.byref(d), PRECISIONS[precision]
     # large sets of pdfs on 2-D grids are swept by tiles, which takes a workspace
-    nb = lib.vup_propagate_tiled_workspace_bytes(mref, dref, prec) if K >= 16384 else 0
+    nb = lib.vup_propagate_tiled_full_workspace_bytes(mref, dref, prec) if K >= 16384 else 0
     if nb:
         ws = torch.empty(nb, dtype=torch.uint8, device=mm.device)
         _check(lib.vup_propagate_tiled(mref, dref, prec, _ptr(ws), nb, _ptr(P), _ptr(Z),

@@ -14,41 +14,46 @@
 // needs one new prefix sum per run. Four consecutive rows (a chunk) advance
 // together: an entry names a bin and the four columns the rows stand at after
 // their run of that bin (rows not at that bin stay where they are and add
-// nothing); with q = sum_i gx_i G[c_i] after each entry, the bin's mass is the
-// step of q. tile_entries (k_ptiles.hpp, part of vup_bin) builds the entries
-// of every chunk, once per model matrix: the next bin is the lowest, the
-// highest, or that of the row furthest behind, whichever rule gives the chunk
-// the fewest entries (rising, falling, other model values along the row). On the sin/cos model at 1024^2 cells and
-// 256 bins that is 1.045 row steps per run; eight rows per entry would take
-// 1.13 and sixteen 1.26. k_pt_scan lists the pdfs that meet each tile, so a
-// batch is full except the last of a list and any order of the pdfs will do.
+// nothing); the bin's mass is sum_i gx_i times row i's step of G. tile_entries
+// (k_ptiles.hpp, part of vup_bin) builds the entries of every chunk, once per
+// model matrix: the next bin is the lowest, the highest, or that of the row
+// furthest behind, whichever rule gives the chunk the fewest entries (rising,
+// falling, other model values along the row). On the sin/cos model at 1024^2
+// cells and 256 bins that is 1.15 row steps per run. k_pt_scan lists the pdfs
+// that meet each tile, so a batch is full except the last of a list and any
+// order of the pdfs will do.
 //
 // Numbers. Column factors are formed by the FP64 recurrence g' = g r,
-// r' = r q (q = exp(-(h/sigma)^2)), rounded to integers in units of 2^-26 of
-// the Gaussian's peak and summed exactly in 32 bits. A row step is one FP64
-// FMA: an LDS word read into the low half of a register pair whose high half
-// holds the exponent of 2^52 is the double 2^52 + G, without a conversion; the
-// 2^52 cancels from the step of q, whose rounding (a few units of gx 2^-26 of
-// the peak) is far below the run's mass. The row factors stay FP64 and carry
-// the fixed-point scale that makes the pdf's whole mass just below 2^32. An
-// entry's step is rounded to an integer and added to its slot with an integer
-// LDS atomic, and a tile's slots are added to the row of P, as integers, with
-// integer global atomics: exact, so the result does not depend on any order.
-// k_pt_final normalises each row by its own total, as the other forms do.
-// Column L1 against FP64 at 1024^2 cells: 1.5e-7 (per-pdf form 5.5e-7).
+// r' = r q (q = exp(-(h/sigma)^2)), in units of the tile's largest factor,
+// rounded to integers of 2^-25 of that or finer and summed exactly in 32 bits.
+// An LDS word read into the low half of a register pair whose high half holds
+// the exponent of 2^52 is the double 2^52 + G, without a conversion, and the
+// difference of two of them is a row's step, exact. The row factors stay FP64
+// and carry the fixed-point scale that makes the pdf's whole mass 2^51 at most.
+// An entry's mass is rounded to that (adding 2^52 puts it into the low 52 bits
+// of the double) and added to its slot with a 64-bit integer LDS atomic; a
+// tile's slots are added, as integers, to the pdf's 64-bit sums with global
+// atomics: exact, so the result does not depend on any order. k_pt_final
+// divides each pdf's sums by their total. So a bin's digits do not depend on
+// the other bins' mass: against FP64 at 1024^2 cells, deviations of 8.5 to 85
+// cells, the bins' relative errors are (median, 99th percentile; per-pdf form
+// in brackets) 2e-8, 5e-8 (6e-8, 1e-6) above a thousandth of the mass, 3e-8,
+// 2e-6 (5e-5, 2e-3) around 1e-6, 7e-7, 1e-5 (6e-3, 9e-2) around 1e-10; columns'
+// L1 error 2.1e-8 (6.4e-8). Sums in 32 bits of the whole mass, two workgroups'
+// worth of LDS less, lost bins below 1e-10 altogether.
 //
 // Measured, 65 536 pdfs on 1024^2 cells, 256 bins, deviations of 8.5 to 85
-// cells: 1.36 ms per-pdf form, 0.58 ms here (k_pt_main 0.56; k_pt_prep, which
-// clears P, k_pt_scan and k_pt_final 0.013, 0.015 and 0.028). k_pt_main issues
-// VALU on 0.65 of the cycles and keeps the LDS pipe busy on about half (per
-// entry and wave 13 VALU instructions, four 4-byte reads and one atomic);
-// lanes whose window covers only part of the tile take 0.33 of the row steps.
+// cells: 1.23 ms per-pdf form, 0.79 ms here (k_pt_main 0.72; k_pt_prep, which
+// clears the sums, k_pt_scan and k_pt_final 0.02, 0.016 and 0.034). k_pt_main
+// issues VALU on 0.73 of the cycles with three waves per SIMD (per entry and
+// wave 17 VALU instructions, four 4-byte reads and one atomic). With 32-bit
+// sums (four waves per SIMD) it took 0.58 ms, 0.66 with three; running sums
+// over the four rows instead of exact steps (13 VALU instructions) 0.75.
 // Integer sums with conversions and FP32 FMAs took 24 VALU instructions per
-// entry (0.74 ms); one wave per workgroup with its own tables left two waves
-// per SIMD (2.2 ms); entries through scalar loads 0.75 ms (the wait for a
-// scalar load is a wait for the LDS too); looking for the tile's pdfs inside
-// the sweep 0.87 ms; eight columns more per batch or pdfs sorted by deviation
-// within 256 no change.
+// entry; one wave per workgroup with its own tables left two waves per SIMD
+// (2.2 ms); entries through scalar loads were slower (the wait for a scalar
+// load is a wait for the LDS too), and so was looking for the tile's pdfs
+// inside the sweep.
 #include <hip/hip_runtime.h>
 
 #include "k_ptiles.hpp"
@@ -64,20 +69,23 @@ constexpr unsigned long long kPNoTile = 1ull;  // tile range of a pdf not in the
 constexpr int kPPart = 16384;      // pdfs a list covers (16-bit positions)
 constexpr long long kPMaxList = 1ll << 27;  // entries of the lists (16 bits each)
 constexpr long long kPMaxBlocks = 65536;
-// narrowest pdf, in cells: below it the mass bound is loose (fewer bits left
-// for the fixed point); such pdfs are left to the per-pdf kernels
-constexpr double kPMinSigma = 0.5;
-// factors in units of 2^-26 of the peak: 64 of them stay below 2^32
-constexpr double kPUnit = 67108863.0;
+// fixed-point mass of a pdf (at most), and the bits of a sum: the words added
+// to it are doubles 2^52 + v, whose other bits a sum of v below 2^52 leaves alone
+constexpr double kPMass = 2251799813685248.0;
+constexpr unsigned long long kPSum = (1ull << 52) - 1ull;
+// recurrences step by at most so many deviations, from so far out (t^2 / 2)
+constexpr double kPMaxStep = 1.0, kPMaxOff = 450.0;
+// -log of a pdf's largest density, in units of its peak
+constexpr double kPMaxExp = 700.0;
 
 struct PtRec {
   uint16_t lo[2], hi[2];  // window
   int k;                  // pdf
   uint32_t pad;
-  double t0[2];           // (x of cell 0 - mu) / sigma
+  double t0[2];           // (x of the window's first cell - mu) / sigma
   double dt[2];           // h / sigma
-  double qq[2];           // exp(-dt^2)
-  double scale;           // fixed-point units per unit of gx gy; 0: not in the tiles
+  double e[2];            // t^2 / 2 of the window's cell nearest the mean
+  double scale;           // fixed-point units per unit of gx gy e^(e[0] + e[1]); 0: not in the tiles
 };
 static_assert(sizeof(PtRec) == 72, "record layout");
 
@@ -102,7 +110,7 @@ struct PtArgs {
   int* counts;                // [tiles][parts] records in each list
   uint32_t* batches;          // list << 8 | batch of the list
   int* state;                 // [0] batches, [1] batches taken by k_pt_main
-  uint32_t* none;             // [K] mass in cells without a bin
+  unsigned long long* acc;    // [K][B + 1] fixed-point mass of each bin and of the cells without
   int* klist;                 // pdfs left to the per-pdf kernel; [K] holds their number
   float* P;
   double* Z;
@@ -133,36 +141,43 @@ __device__ __forceinline__ double pt_exp(double a) {
 }
 
 // ---------------------------------------------------------------------------
-// per pdf: window, fixed-point scale; clears the rows of P
+// per pdf: window, fixed-point scale; clears the sums
 // ---------------------------------------------------------------------------
-// upper bound of the sum of the factors of window cells lo .. hi, in cells: a
-// unimodal function's sum is at most its integral plus its largest value
-__device__ __forceinline__ double mass_bound(double lo, double h, int jlo, int jhi, double mu,
-                                             double sigma) {
-  const double rs = 0.7071067811865476 / sigma;
-  const float ta = (float)((lo + (jlo + 0.5) * h - mu) * rs);
-  const float tb = (float)((lo + (jhi + 0.5) * h - mu) * rs);
-  // (a pdf so wide that its factors differ by less than the bound's margin: the
-  // cells themselves; further out ta and tb would lose their digits)
-  if (!(tb - ta > 1e-4f)) return (double)(jhi - jlo + 1);
-  const double area = 1.2533141373155003 * sigma / h * (double)(erff(tb) - erff(ta));
-  return area * (1.0 + 1e-5) + 1.0;
+// e - t^2 / 2, exactly 0 where e is that t^2 / 2
+__device__ __forceinline__ double pt_arg(double e, double t) {
+#pragma clang fp contract(off)
+  return e - 0.5 * (t * t);
+}
+
+// one axis of a pdf's record
+__device__ __forceinline__ void pt_axis(PtRec& r, int d, double lo, double hi, int n, int jlo,
+                                        int jhi, double mu, double sigma) {
+  const double h = (hi - lo) / n, rs = 1.0 / sigma;
+  double c = floor((mu - lo) / h);
+  c = c >= (double)jlo ? c : (double)jlo;
+  c = c <= (double)jhi ? c : (double)jhi;
+  r.lo[d] = (uint16_t)jlo;
+  r.hi[d] = (uint16_t)jhi;
+  r.t0[d] = (cell_centre(lo, hi, n, jlo) - mu) * rs;
+  r.dt[d] = h * rs;
+  r.e[d] = -pt_arg(0.0, fma(c - jlo, r.dt[d], r.t0[d]));
+}
+
+// Upper bound of the sum of a window's factors in units of its largest one, for
+// W of its cells: on either side of the mean they fall from at most 1, so they
+// add up to at most 1 and the integral from there on (Mills' ratio: at most
+// sqrt(pi / 2) deviations).
+__device__ __forceinline__ double mass_bound(int W, double dt) {
+  return fmin((double)W, 2.0 + 2.5066282746310007 / dt);
 }
 
 __global__ __launch_bounds__(256) void k_pt_prep(PtArgs a) {
   const long long t0 = (long long)blockIdx.x * 256 + threadIdx.x;
   if (t0 == 0) a.klist[a.K] = a.state[0] = a.state[1] = 0;
-  // the rows of P hold integers until k_pt_final; rows of pdfs that are not
-  // in the tiles are written whole by the per-pdf kernel
-  const long long words = a.K * a.B, step = (long long)gridDim.x * 256;
-  uint32_t* Pu = reinterpret_cast<uint32_t*>(a.P);
-  if (((uintptr_t)a.P & 15) == 0) {
-    uint4* P4 = reinterpret_cast<uint4*>(Pu);
-    for (long long i = t0; i < words / 4; i += step) P4[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (long long i = words / 4 * 4 + t0; i < words; i += step) Pu[i] = 0u;
-  } else {
-    for (long long i = t0; i < words; i += step) Pu[i] = 0u;
-  }
+  const long long words = a.K * (a.B + 1), step = (long long)gridDim.x * 256;
+  ulonglong2* acc2 = reinterpret_cast<ulonglong2*>(a.acc);
+  for (long long i = t0; i < words / 2; i += step) acc2[i] = make_ulonglong2(0ull, 0ull);
+  if (t0 == 0 && (words & 1)) a.acc[words - 1] = 0ull;
   const long long k = t0;
   PtRec r = {};
   unsigned long long bb = kPNoTile;
@@ -172,36 +187,19 @@ __global__ __launch_bounds__(256) void k_pt_prep(PtArgs a) {
     int lo0, hi0, lo1, hi1;
     const bool ok0 = axis_window(a.lo[0], a.hi[0], a.n[0], mu0, s0, a.ns, lo0, hi0);
     const bool ok1 = axis_window(a.lo[1], a.hi[1], a.n[1], mu1, s1, a.ns, lo1, hi1);
-    const double h0 = (a.hi[0] - a.lo[0]) / a.n[0], h1 = (a.hi[1] - a.lo[1]) / a.n[1];
-    // in the tiles: valid pdfs with the mean inside the grid and a deviation
-    // of at least kPMinSigma cells (so the mass bound is within a small factor
-    // of the mass; invalid, empty and very narrow ones take the per-pdf kernel)
-    const bool in = ok0 && ok1 && lo0 <= hi0 && lo1 <= hi1 && mu0 >= a.lo[0] &&
-                    mu0 <= a.hi[0] && mu1 >= a.lo[1] && mu1 <= a.hi[1] &&
-                    s0 >= kPMinSigma * h0 && s1 >= kPMinSigma * h1;
     r.k = (int)k;
+    // in the tiles: all but invalid pdfs, empty windows and densities at the end
+    // of FP64's range (or past it), which take the per-pdf kernel
+    const bool in = ok0 && ok1 && lo0 <= hi0 && lo1 <= hi1;
     if (in) {
-      r.lo[0] = (uint16_t)lo0;
-      r.lo[1] = (uint16_t)lo1;
-      r.hi[0] = (uint16_t)hi0;
-      r.hi[1] = (uint16_t)hi1;
-      const double rs0 = 1.0 / s0, rs1 = 1.0 / s1;
-      r.t0[0] = (cell_centre(a.lo[0], a.hi[0], a.n[0], 0) - mu0) * rs0;
-      r.t0[1] = (cell_centre(a.lo[1], a.hi[1], a.n[1], 0) - mu1) * rs1;
-      r.dt[0] = h0 * rs0;
-      r.dt[1] = h1 * rs1;
-      r.qq[0] = pt_exp(-r.dt[0] * r.dt[0]);
-      r.qq[1] = pt_exp(-r.dt[1] * r.dt[1]);
-      const double m = mass_bound(a.lo[0], h0, lo0, hi0, mu0, s0) *
-                       mass_bound(a.lo[1], h1, lo1, hi1, mu1, s1);
-      // every entry of the tiles it meets rounds by at most half a unit
-      const double ent = (double)((lo1 / kPX - hi1 / kPX - 1) * (lo0 / kPY - hi0 / kPY - 1)) *
-                         (2 * kPCh * kPEnt);
-      r.scale = (4294967296.0 - 1048576.0 - ent) / (m * (1.0 + 1.0 / 65536));
+      pt_axis(r, 0, a.lo[0], a.hi[0], a.n[0], lo0, hi0, mu0, s0);
+      pt_axis(r, 1, a.lo[1], a.hi[1], a.n[1], lo1, hi1, mu1, s1);
+    }
+    if (in && r.e[0] + r.e[1] <= kPMaxExp) {
+      r.scale = kPMass / (mass_bound(hi0 - lo0 + 1, r.dt[0]) * mass_bound(hi1 - lo1 + 1, r.dt[1]));
       bb = (unsigned long long)(lo1 / kPX) | ((unsigned long long)(hi1 / kPX) << 16) |
            ((unsigned long long)(lo0 / kPY) << 32) | ((unsigned long long)(hi0 / kPY) << 48);
     }
-    a.none[k] = 0u;
     a.rec[k] = r;
     a.bbox[k] = bb;
   }
@@ -299,17 +297,17 @@ static_assert(kPWCh * kPWaves == 2 * kPCh && kPWRows == 32, "a wave's rows lie i
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-__global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
+__global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
   __shared__ uint32_t sG[(kPX + 1) * 64];        // [column][lane] prefix sums
   // [slot][lane xor slot] sums; slot kPSlots: cells without a bin, then a
   // slot for bins outside the pass
-  __shared__ uint32_t sH[(kPSlots + 2) * 64];
-  __shared__ uint32_t sOff[64];                  // rows of P of the batch (element offsets)
+  __shared__ unsigned long long sH[(kPSlots + 2) * 64];
+  __shared__ uint32_t sOff[64];                  // the batch's rows of sums (element offsets)
   __shared__ uint32_t wtot[kPWaves][64];
   __shared__ int snext;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t lane4 = 4u * (uint32_t)lane;
+  const uint32_t lane4 = 4u * (uint32_t)lane, lane8 = 8u * (uint32_t)lane;
   // byte n of a word over the lane's byte offset: v_perm_b32 selectors, kept
   // in vector registers (an instruction reads one scalar register)
   uint32_t sel0 = 0x0c0c0400u, sel1 = 0x0c0c0500u, sel2 = 0x0c0c0600u, sel3 = 0x0c0c0700u;
@@ -317,8 +315,7 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
   uint32_t two52 = 0x43300000u;  // high word of 2^52 (kept from the optimiser)
   asm("" : "+v"(two52));
   if (w == 0) sG[lane] = 0u;
-  for (int i = threadIdx.x; i < (kPSlots + 2) * 64; i += 256) sH[i] = 0u;
-  uint32_t* Pu = reinterpret_cast<uint32_t*>(a.P);
+  for (int i = threadIdx.x; i < (kPSlots + 2) * 64; i += 256) sH[i] = 0ull;
   // workgroups take batches until none is left: the first by their index, the
   // next ones from a counter
   const int nbatches = a.state[0];
@@ -372,21 +369,40 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
       rmask = bits(r.lo[0], r.hi[0], r0, kPWRows);
     }
     const double dt0 = r.dt[0], dt1 = r.dt[1];
-    const double ty0 = fma((double)r0, dt0, r.t0[0]), tx0 = fma((double)c0, dt1, r.t0[1]);
-    const double S0 = r.scale * (1.0 / kPUnit);  // row factors carry the fixed-point scale
+    // A factor is formed as exp(e - t^2 / 2), the row's with e of the window's
+    // cell nearest the mean, the column's with that of the tile's: both are at
+    // most 1, and what the column's exceed the window's by, exp(e[1] - ec),
+    // goes to the row factors, with the fixed-point scale.
+    const int ca = max((int)r.lo[1], tx * kPX), cb = min((int)r.hi[1], tx * kPX + kPX - 1);
+    const double ta = fma((double)(ca - r.lo[1]), dt1, r.t0[1]);
+    const double tb = fma((double)(cb - r.lo[1]), dt1, r.t0[1]);
+    const double ec = ta >= 0.0 ? -pt_arg(0.0, ta) : tb <= 0.0 ? -pt_arg(0.0, tb) : r.e[1];
+    const double er = r.e[1] - ec;
+    // The columns' unit 2^-cexp: the finest power of two (so that the row
+    // factors can undo it exactly) with their sum's bound below 2^32. (The bound
+    // in FP32 is at least an ulp below a power of two or at it, so the 64 halves
+    // of a unit that rounding may add stay within 32 bits.)
+    const float cmass = fminf((float)(cb - ca + 1), 2.0001f + 2.5067f * __builtin_amdgcn_rcpf((float)dt1));
+    const int cexp = 32 - __builtin_amdgcn_frexp_expf(cmass);
+    const double S0 = ldexp(r.scale, -cexp), unit = ldexp(1.0, cexp);
+    const double ty0 = fma((double)(r0 - r.lo[0]), dt0, r.t0[0]);
+    const double tx0 = fma((double)(c0 - r.lo[1]), dt1, r.t0[1]);
     // The recurrences start at the wave's first row and column, which may lie
-    // outside the window, n dt deviations further out (n = 15 columns, 31
-    // rows). A start beyond t = 37 is 0 in FP64 and stays 0; that loses nothing
-    // while n dt <= 30, since factors beyond t = 7 are below the units used.
-    // dt <= 2 (kPMinSigma), so the columns are safe, and the rows when they
-    // start again half way.
-    static_assert((kPWCols - 1) / kPMinSigma <= 30 && (kPWRows / 2 - 1) / kPMinSigma <= 30, "range");
-    const bool restart = __any(valid && (kPWRows - 1) * dt0 > 30.0);
+    // outside the window, n dt deviations further out (15 columns, 31 rows, or
+    // 15 when the rows start again half way). A factor e^-36 below the largest
+    // is below the units used; one that counts has a start above e^-620 while
+    // n dt <= 16 and e <= kPMaxOff, so it is never lost to underflow. Pdfs
+    // narrower than a cell, and means far outside the grid, have each of their
+    // factors formed by itself (with the t of k_pt_prep, so that the largest is
+    // exactly 1 however narrow the pdf).
+    const bool direct = __any(valid && (fmax(dt0, dt1) > kPMaxStep || fmax(r.e[0], r.e[1]) > kPMaxOff));
+    const bool restart = __any(valid && (kPWRows - 1) * dt0 > 16.0);
+    static_assert((kPWCols - 1) * kPMaxStep <= 16 && (kPWRows / 2 - 1) * kPMaxStep <= 16, "range");
     uint32_t G[kPWCols], sum = 0u;
-    {
-      double g = kPUnit * pt_exp(-0.5 * tx0 * tx0);
+    if (!direct) {
+      double g = unit * pt_exp(pt_arg(ec, tx0));
       double q = pt_exp(fmin(-(tx0 + 0.5 * dt1) * dt1, 700.0));
-      const double qq = r.qq[1];
+      const double qq = pt_exp(-dt1 * dt1);
 #pragma unroll
       for (int c = 0; c < kPWCols; ++c) {
         // + 2^52: the low word is g rounded to an integer
@@ -395,6 +411,18 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
         G[c] = sum;
         g *= q;
         q *= qq;
+      }
+    } else {  // (uniform over the workgroup)
+      __syncthreads();  // the last batch's readers of sG are done
+#pragma unroll 1
+      for (int c = 0; c < kPWCols; ++c) {
+        const double g = unit * pt_exp(fmin(pt_arg(ec, fma((double)(c0 + c - r.lo[1]), dt1, r.t0[1])), 0.0));
+        sG[(kPWCols * w + c + 1) * 64 + lane] = (uint32_t)__double_as_longlong(g + 4503599627370496.0);
+      }
+#pragma unroll
+      for (int c = 0; c < kPWCols; ++c) {
+        sum += sG[(kPWCols * w + c + 1) * 64 + lane] & bit_mask(cmask, c);
+        G[c] = sum;
       }
     }
     wtot[w][lane] = sum;
@@ -405,21 +433,21 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
     for (int v = 0; v < kPWaves - 1; ++v) before += v < w ? wtot[v][lane] : 0u;
 #pragma unroll
     for (int c = 0; c < kPWCols; ++c) sG[(kPWCols * w + c + 1) * 64 + lane] = before + G[c];
-    if (w == 0) sOff[lane] = (uint32_t)(valid ? k : 0) * (uint32_t)a.B;
+    if (w == 0) sOff[lane] = (uint32_t)(valid ? k : 0) * (uint32_t)(a.B + 1);
     __syncthreads();
     for (int ps = 0; ps < passes; ++ps) {
       const int base = tmn + ps * kPSlots;
       if (have) {
-        double g = S0 * pt_exp(-0.5 * ty0 * ty0);
+        double g = S0 * pt_exp(pt_arg(r.e[0], ty0) + er);
         double q = pt_exp(fmin(-(ty0 + 0.5 * dt0) * dt0, 700.0));
-        const double qq = r.qq[0];
+        const double qq = pt_exp(-dt0 * dt0);
         uint32_t rm = rmask;
         // buffers of prefix sums as doubles 2^52 + G: only the low words change
-        u32x2 A[2 * kPR], Bf[2 * kPR];
+        u32x2 A[2 * kPR], Bf[2 * kPR], Cf[2 * kPR];
 #pragma unroll
         for (int j = 0; j < 2 * kPR; ++j) {
-          A[j][0] = Bf[j][0] = 0u;
-          A[j][1] = Bf[j][1] = two52;
+          A[j][0] = Bf[j][0] = Cf[j][0] = 0u;
+          A[j][1] = Bf[j][1] = Cf[j][1] = two52;
         }
         int cn = __builtin_amdgcn_readfirstlane(cs[0].n);
         const uint2* ev = a.entries + __builtin_amdgcn_readfirstlane(cs[0].first);
@@ -428,17 +456,26 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
         for (int ch = 0; ch < kPWCh; ++ch) {
           if (restart && ch == kPWCh / 2) {
             const double t = fma((double)(kPWRows / 2), dt0, ty0);
-            g = S0 * pt_exp(-0.5 * t * t);
+            g = S0 * pt_exp(pt_arg(r.e[0], t) + er);
             q = pt_exp(fmin(-(t + 0.5 * dt0) * dt0, 700.0));
           }
           double gx[kPR];
 #pragma unroll
           for (int i = 0; i < kPR; ++i) {
-            const long long b = __double_as_longlong(g);
-            const uint32_t on = bit_mask(rm, i);
-            gx[i] = __hiloint2double((int)((uint32_t)(b >> 32) & on), (int)((uint32_t)b & on));
+            gx[i] = g;
             g *= q;
             q *= qq;
+          }
+          if (direct) {
+#pragma unroll
+            for (int i = 0; i < kPR; ++i)
+              gx[i] = S0 * pt_exp(fmin(pt_arg(r.e[0], fma((double)(r0 + kPR * ch + i - r.lo[0]), dt0, r.t0[0])), 0.0) + er);
+          }
+#pragma unroll
+          for (int i = 0; i < kPR; ++i) {
+            const long long b = __double_as_longlong(gx[i]);
+            const uint32_t on = bit_mask(rm, i);
+            gx[i] = __hiloint2double((int)((uint32_t)(b >> 32) & on), (int)((uint32_t)b & on));
           }
           const bool any = __any((rm & 15u) != 0u);
           rm >>= kPR;
@@ -451,11 +488,10 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
             ent = ev[lane];
           }
           if (!any) continue;  // no pdf of the batch has these rows
-          // the sum at G = 0, by add()'s operations in add()'s order: an entry
-          // that moves no row over mass then gives exactly 0
-          double last = gx[0] * 4503599627370496.0;
+          // every row stands at column 0 (the second half of Cf is what the
+          // first entry's sums are subtracted from)
 #pragma unroll
-          for (int j = 1; j < kPR; ++j) last = __builtin_fma(gx[j], 4503599627370496.0, last);
+          for (int j = 0; j < kPR; ++j) Cf[kPR + j][0] = 0u;
           for (int f = 0; f < n; f += 64) {
             const int m = min(64, n - f);  // even
             uint2 e = first;
@@ -479,33 +515,50 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
                 o[4 * u + 3][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel3));
               }
             };
-            auto add = [&](int i, const u32x2 (&o)[2 * kPR]) {
+            // the bin's mass: the rows' steps of G (exact differences) times
+            // their factors, rounded once to the fixed point
+            auto add = [&](int i, const u32x2 (&o)[2 * kPR], const u32x2 (&before)[2 * kPR]) {
 #pragma unroll
               for (int u = 0; u < 2; ++u) {
-                double sum = gx[0] * __builtin_bit_cast(double, o[4 * u]);
+                double sum = 0.0;
 #pragma unroll
-                for (int j = 1; j < kPR; ++j)
-                  sum = __builtin_fma(gx[j], __builtin_bit_cast(double, o[4 * u + j]), sum);
-                const uint32_t v =
-                    (uint32_t)__double_as_longlong((sum - last) + 6755399441055744.0);
-                last = sum;
+                for (int j = 0; j < kPR; ++j) {
+                  const double d = __builtin_bit_cast(double, o[4 * u + j]) -
+                                   __builtin_bit_cast(double, u ? o[j] : before[kPR + j]);
+                  sum = j ? __builtin_fma(gx[j], d, sum) : gx[0] * d;
+                }
                 const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)slot, i + u);
-                uint32_t* h = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sH) + (at ^ lane4));
-                __hip_atomic_fetch_add(h, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                unsigned long long* h = reinterpret_cast<unsigned long long*>(
+                    reinterpret_cast<char*>(sH) + (at ^ lane8));
+                __hip_atomic_fetch_add(
+                    h, (unsigned long long)__double_as_longlong(sum + 4503599627370496.0),
+                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
               }
             };
-            // two entries at a time, the reads of the next two in flight
+            // two entries at a time, the reads of the next two in flight; three
+            // buffers, as the sums of one pair are subtracted from the next one's
             load(0, A);
-            for (int i = 0;; i += 4) {
-              const bool more = i + 2 < m, more2 = i + 4 < m;
-              if (more) load(i + 2, Bf);
+            for (int i = 0;; i += 6) {
+              if (i + 2 < m) load(i + 2, Bf);
               __builtin_amdgcn_sched_barrier(0);
-              add(i, A);
-              if (!more) break;
-              if (more2) load(i + 4, A);
+              add(i, A, Cf);
+              if (i + 2 >= m) {
+#pragma unroll
+                for (int j = 0; j < kPR; ++j) Cf[kPR + j] = A[kPR + j];
+                break;
+              }
+              if (i + 4 < m) load(i + 4, Cf);
               __builtin_amdgcn_sched_barrier(0);
-              add(i + 2, Bf);
-              if (!more2) break;
+              add(i + 2, Bf, A);
+              if (i + 4 >= m) {
+#pragma unroll
+                for (int j = 0; j < kPR; ++j) Cf[kPR + j] = Bf[kPR + j];
+                break;
+              }
+              if (i + 6 < m) load(i + 6, A);
+              __builtin_amdgcn_sched_barrier(0);
+              add(i + 4, Cf, Bf);
+              if (i + 6 >= m) break;
             }
           }
         }
@@ -520,10 +573,10 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
       auto give = [&](int b, int p) {  // bin base + b of pdf p
         const int s = b0 + b < kPSlots ? b0 + b : b0 + b - kPSlots;
         const int at = s * 64 + (p ^ (s & 63));
-        const uint32_t v = sH[at], o = sOff[p] + (uint32_t)(base + b);
-        sH[at] = 0u;
-        // (a slot without mass may hold a few units of negative rounding noise)
-        if (v - 1u < 0xFFF80000u && b < span) __hip_atomic_fetch_add(&Pu[o], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long v = sH[at] & kPSum;
+        const uint32_t o = sOff[p] + (uint32_t)(base + b);
+        sH[at] = 0ull;
+        if (v && b < span) __hip_atomic_fetch_add(&a.acc[o], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
       if (span > 32) {
 #pragma unroll 4
@@ -543,54 +596,54 @@ __global__ __launch_bounds__(256, 4) void k_pt_main(PtArgs a) {
     }
     if (tnone && w == 0) {
       const int at = kPSlots * 64 + (lane ^ (kPSlots & 63));
-      const uint32_t v = sH[at];
-      sH[at] = 0u;
-      if (valid && v - 1u < 0xFFF80000u)
-        __hip_atomic_fetch_add(&a.none[k], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long v = sH[at] & kPSum;
+      sH[at] = 0ull;
+      if (valid && v)
+        __hip_atomic_fetch_add(&a.acc[sOff[lane] + (uint32_t)a.B], v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   }
 }
 
 // ---------------------------------------------------------------------------
-// per pdf: normalise the row of integers by its total; a wave per row
+// per pdf: the row of P, its sums divided by their total; a wave per row
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_pt_final(PtArgs a) {
   const int lane = threadIdx.x & 63;
-  const long long at = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (at >= a.K) return;
-  const double scale = a.rec[at].scale;
-  const long long k = a.rec[at].k;
+  const long long k = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (k >= a.K) return;
+  const double scale = a.rec[k].scale;
   if (!(scale > 0.0)) return;  // the per-pdf kernel's row
-  const uint32_t* u = reinterpret_cast<const uint32_t*>(a.P) + k * a.B;
+  const unsigned long long* u = a.acc + k * (a.B + 1);
   float* p = a.P + k * a.B;
-  double sum = 0.0;
-  if (a.B <= 256) {
-    uint32_t v[4];
+  // (sums below 2^52: a double holds them)
+  double sum = 0.0, tot;
+  if (a.B < 320) {
+    double v[5];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[i] = lane + 64 * i < a.B ? u[lane + 64 * i] : 0u;
-      sum += (double)v[i];
+    for (int i = 0; i < 5; ++i) {
+      v[i] = lane + 64 * i <= a.B ? (double)u[lane + 64 * i] : 0.0;
+      sum += v[i];
     }
-    const double tot = wave_sum(sum) + (double)a.none[k];
+    tot = wave_sum(sum);
     const double f = 1.0 / tot;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (lane + 64 * i < a.B) p[lane + 64 * i] = (float)((double)v[i] * f);
-    if (a.Z && lane == 0) a.Z[k] = tot / scale;
-    return;
+    for (int i = 0; i < 5; ++i)
+      if (lane + 64 * i < a.B) p[lane + 64 * i] = (float)(v[i] * f);
+  } else {
+    for (int b = lane; b <= a.B; b += 64) sum += (double)u[b];
+    tot = wave_sum(sum);
+    const double f = 1.0 / tot;
+    for (int b = lane; b < a.B; b += 64) p[b] = (float)((double)u[b] * f);
   }
-  for (int b = lane; b < a.B; b += 64) sum += (double)u[b];
-  const double tot = wave_sum(sum) + (double)a.none[k];
-  const double f = 1.0 / tot;
-  for (int b = lane; b < a.B; b += 64) p[b] = (float)((double)u[b] * f);
-  if (a.Z && lane == 0) a.Z[k] = tot / scale;
+  if (a.Z && lane == 0) a.Z[k] = tot / scale * pt_exp(-(a.rec[k].e[0] + a.rec[k].e[1]));
 }
 
 constexpr size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct PtLayout {
-  size_t rec, bbox, lists, counts, batches, state, none, klist, bytes;
+  size_t rec, bbox, lists, counts, batches, state, klist, acc;  // acc: to the end
 };
 
 PtLayout pt_layout(long long ntiles, long long K) {
@@ -602,10 +655,23 @@ PtLayout pt_layout(long long ntiles, long long K) {
   L.counts = L.lists + al256((size_t)nlists * kPPart * 2);
   L.batches = L.counts + al256((size_t)nlists * 4);
   L.state = L.batches + al256((size_t)nlists * (kPPart / 64) * 4);
-  L.none = L.state + 256;
-  L.klist = L.none + al256((size_t)K * 4);
-  L.bytes = L.klist + al256((size_t)(K + 1) * 4);
+  L.klist = L.state + 256;
+  L.acc = L.klist + al256((size_t)(K + 1) * 4);
   return L;
+}
+
+// workspace of one pass over kg pdfs
+size_t pt_pass_bytes(long long ntiles, int B, long long kg) {
+  return pt_layout(ntiles, kg).acc + (size_t)kg * (size_t)(B + 1) * 8;
+}
+
+// pdfs of a pass when it is up to the library: all, or even shares that keep
+// the sums within about 256 MB (and the batches full)
+long long pt_share(long long K, int B) {
+  long long most = (1ll << 25) / (B + 1);
+  if (most < 2 * kPtMinK) most = 2 * kPtMinK;
+  const long long passes = (K + most - 1) / most;
+  return (K + passes - 1) / passes;
 }
 
 int pt_div(int n, int m) { return (n + m - 1) / m; }
@@ -639,11 +705,26 @@ bool propagate_tiled_applies(const vup_mm& mm, const vup_dists& d, int prec) {
 }
 
 size_t propagate_tiled_ws_bytes(const vup_mm& mm, long long K) {
-  return pt_layout(pt_tiles(mm), K).bytes;
+  return pt_layout(pt_tiles(mm), K).acc + al256((size_t)K * 4);
 }
 
-hipError_t launch_propagate_tiled(const vup_mm& mm, const vup_dists& d, void* ws, float* P,
-                                  double* Z, hipStream_t s) {
+size_t propagate_tiled_full_bytes(const vup_mm& mm, long long K) {
+  const size_t least = propagate_tiled_ws_bytes(mm, K);
+  const size_t full = pt_pass_bytes(pt_tiles(mm), mm.B, pt_share(K, mm.B));
+  return full > least ? full : least;
+}
+
+long long propagate_tiled_pass(const vup_mm& mm, long long K, size_t ws_bytes) {
+  const long long ntiles = pt_tiles(mm);
+  long long kg = pt_share(K, mm.B);
+  for (long long passes = (K + kg - 1) / kg; kg >= kPtMinK; ++passes, kg = (K + passes - 1) / passes)
+    if (pt_pass_bytes(ntiles, mm.B, kg) <= ws_bytes) return kg;
+  return 0;
+}
+
+// one pass
+static hipError_t launch_pass(const vup_mm& mm, const vup_dists& d, void* ws, float* P, double* Z,
+                              hipStream_t s) {
   PtArgs a{};
   for (int i = 0; i < 2; ++i) {
     a.n[i] = mm.grid.n[i];
@@ -675,19 +756,32 @@ hipError_t launch_propagate_tiled(const vup_mm& mm, const vup_dists& d, void* ws
   a.counts = reinterpret_cast<int*>(base + L.counts);
   a.batches = reinterpret_cast<uint32_t*>(base + L.batches);
   a.state = reinterpret_cast<int*>(base + L.state);
-  a.none = reinterpret_cast<uint32_t*>(base + L.none);
+  a.acc = reinterpret_cast<unsigned long long*>(base + L.acc);
   a.klist = reinterpret_cast<int*>(base + L.klist);
   a.P = P;
   a.Z = Z;
   const long long pb = (d.K + 255) / 256;
   hipLaunchKernelGGL(k_pt_prep, dim3((unsigned)(pb > 2048 ? pb : 2048)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_pt_scan, dim3((unsigned)(ntiles * a.parts)), dim3(kPScan), 0, s, a);
-  // as many workgroups as fit on the GPU (four per CU)
-  hipLaunchKernelGGL(k_pt_main, dim3(1024), dim3(256), 0, s, a);
+  // as many workgroups as fit on the GPU (three per CU)
+  hipLaunchKernelGGL(k_pt_main, dim3(768), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_pt_final, dim3((unsigned)((d.K + 3) / 4)), dim3(256), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_propagate_list(mm, d, a.klist, a.klist + d.K, P, Z, s);
+}
+
+hipError_t launch_propagate_tiled(const vup_mm& mm, const vup_dists& d, long long kg, void* ws,
+                                  float* P, double* Z, hipStream_t s) {
+  for (long long k = 0; k < d.K; k += kg) {
+    vup_dists part = d;
+    part.K = d.K - k < kg ? d.K - k : kg;
+    part.mu = d.mu + 2 * k;
+    part.sigma = d.sigma + 2 * k;
+    const hipError_t e = launch_pass(mm, part, ws, P + k * mm.B, Z ? Z + k : nullptr, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace vup

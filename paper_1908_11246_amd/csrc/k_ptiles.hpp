@@ -15,7 +15,7 @@ constexpr int kPL = 64;            // rows of a block of entries
 constexpr int kPR = 4;             // rows of a chunk
 constexpr int kPCh = kPL / kPR;    // chunks of a block
 constexpr int kPEnt = 128;         // entries a chunk may have
-constexpr int kPSlots = 78;        // bins a pass over a tile covers: four workgroups' LDS fit on a CU
+constexpr int kPSlots = 66;        // bins a pass over a tile covers: three workgroups' LDS fit on a CU
 constexpr int kPNoBin = 0xFFFF;    // entry of cells without a bin
 
 // one chunk's entries
@@ -47,12 +47,13 @@ struct PtEntArgs {
 };
 constexpr unsigned long long kPUnfit = 1ull << 40;
 
-// byte offset of a slot's lane 0 in the sums of k_pt_main: slot s, lane l sits
-// at dword 64 s + (l xor s mod 64), so that both the lanes of a slot and the
-// slots of a lane fall on distinct banks
+// byte offset of a slot's lane 0 in the sums of k_pt_main (8 bytes each): slot
+// s, lane l is number 64 s + (l xor s mod 64), so that both the lanes of a slot
+// and the slots of a lane fall evenly on the banks
 __device__ __forceinline__ uint32_t slot_code(int s) {
-  return (uint32_t)s * 256u + ((uint32_t)s & 63u) * 4u;
+  return (uint32_t)s * 512u + ((uint32_t)s & 63u) * 8u;
 }
+static_assert((kPSlots + 2) * 512 <= 65536, "16 bits of an entry");
 
 template <int CTRL>
 __device__ __forceinline__ int quad(int v) {

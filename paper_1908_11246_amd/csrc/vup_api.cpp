@@ -222,6 +222,13 @@ size_t vup_propagate_tiled_workspace_bytes(const vup_mm* mm, const vup_dists* d,
   return vup::propagate_tiled_ws_bytes(*mm, d->K);
 }
 
+size_t vup_propagate_tiled_full_workspace_bytes(const vup_mm* mm, const vup_dists* d,
+                                                int32_t precision) {
+  if (check_mm(mm) || check_dists(d, mm->grid.ndim)) return 0;
+  if (!vup::propagate_tiled_applies(*mm, *d, precision)) return 0;
+  return vup::propagate_tiled_full_bytes(*mm, d->K);
+}
+
 int vup_propagate_tiled(const vup_mm* mm, const vup_dists* d, int32_t precision, void* ws,
                         size_t ws_bytes, float* P, double* Z, void* stream) {
   int r = check_mm(mm);
@@ -235,8 +242,10 @@ int vup_propagate_tiled(const vup_mm* mm, const vup_dists* d, int32_t precision,
   if (!ws) return fail(VUP_EWORKSPACE, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(VUP_EWORKSPACE, "workspace not 256-byte aligned");
   if (ws_bytes < need) return fail(VUP_EWORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, need);
+  const long long kg = vup::propagate_tiled_pass(*mm, d->K, ws_bytes);
+  if (kg == 0) return vup_propagate(mm, d, precision, P, Z, stream);
   if ((r = check_device())) return r;
-  return launched(vup::launch_propagate_tiled(*mm, *d, ws, P, Z, (hipStream_t)stream),
+  return launched(vup::launch_propagate_tiled(*mm, *d, kg, ws, P, Z, (hipStream_t)stream),
                   "vup_propagate_tiled");
 }
 

@@ -67,8 +67,12 @@ constexpr int kTilesPay = 1, kTilesNot = 2;
 void tile_entry_sizes(const vup_grid& g, size_t* ents, size_t* chunks, size_t* blocks);
 bool propagate_tiled_applies(const vup_mm& mm, const vup_dists& d, int prec);
 size_t propagate_tiled_ws_bytes(const vup_mm& mm, long long K);
-hipError_t launch_propagate_tiled(const vup_mm& mm, const vup_dists& d, void* ws, float* P,
-                                  double* Z, hipStream_t s);
+// workspace for the fewest passes, and the pdfs of a pass that ws_bytes allow
+// (0: too few for the tiles to pay)
+size_t propagate_tiled_full_bytes(const vup_mm& mm, long long K);
+long long propagate_tiled_pass(const vup_mm& mm, long long K, size_t ws_bytes);
+hipError_t launch_propagate_tiled(const vup_mm& mm, const vup_dists& d, long long kg, void* ws,
+                                  float* P, double* Z, hipStream_t s);
 // the run form for the *kcount distributions klist[0 .. *kcount) (device)
 hipError_t launch_propagate_list(const vup_mm& mm, const vup_dists& d, const int* klist,
                                  const int* kcount, float* P, double* Z, hipStream_t s);

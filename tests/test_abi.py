@@ -398,3 +398,31 @@ def test_propagate_tiled_validation(lib):
     assert call(dists(K=-1), ws, nb) == EINVAL
     assert call(dists(K=5), None, 0, P=None) == EINVAL
     assert call(dists(), ws, nb, prec=9) == EINVAL
+
+
+def test_propagate_tiled_full_workspace(lib):
+    """The full workspace adds 8 (B + 1) bytes per pdf of a share to the least
+    one's lists, and is 0 where the least one is."""
+    d = vup.VupDists()
+    d.K, d.ncomp, d.ndim, d.n_sigma = 16384, 1, 2, 4.0
+    d.mu, d.sigma, d.weight = 0x1000, 0x2000, None
+
+    def sizes(mm, K, prec=0):
+        d.K = K
+        return [f(ctypes.byref(mm), ctypes.byref(d), prec) for f in
+                (lib.vup_propagate_tiled_workspace_bytes,
+                 lib.vup_propagate_tiled_full_workspace_bytes)]
+
+    for B in (1, 16, 300, 4096):
+        mm = _fake_mm(lib, n=(256, 256), B=B)
+        assert sizes(mm, 20000) == [0, 0]  # unresolved sweep form
+        mm.sweep = 2
+        assert sizes(mm, 16383) == [0, 0] and sizes(mm, 20000, prec=1) == [0, 0]
+        for K in (16384, 20000, 70001):
+            least, full = sizes(mm, K)
+            shares = -(-K // max(32768, (1 << 25) // (B + 1)))
+            kg = -(-K // shares)
+            sums = 8 * (B + 1) * kg
+            lists = 84 * kg + 8 * -(-kg // 16384) * 33 * 1024
+            assert full >= least
+            assert full == least or lists + sums <= full <= lists + sums + 4096

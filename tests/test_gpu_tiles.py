@@ -189,3 +189,100 @@ def test_very_wide_pdfs(vup, orc):
     # FP32 output of sums with far more bits: the bar of the FP32 columns
     assert np.isfinite(P).all() and np.abs(P - Po).sum(1).max() <= 2e-5
     np.testing.assert_allclose(Z, Zo[:, 0], rtol=2e-6)
+
+
+# A column factor is a whole number of units of 2^-25 of the tile's largest
+# factor or finer, so within 4 deviations (factors above e^-8) it is off by at
+# most e^8 2^-26 = 4.4e-5 of itself; row factors are FP64; a bin's entry is
+# rounded to 2^-51 of a bound of the pdf's mass (at most about 8 times the mass,
+# for a mean in a corner of the grid), and a bin has some hundreds of entries in
+# these windows: 1e-12 of the mass. The output is FP32.
+REL, ABS = np.exp(8.0) * 2.0 ** -26 + 2.0 ** -24, 1e-12
+
+
+@pytest.mark.parametrize("n,B,cells", [((256, 256), 64, (1.0, 30.0)), ((300, 200), 40, (0.5, 4.0)),
+                                       ((512, 512), 128, (8.0, 60.0))])
+def test_small_bins_keep_their_digits(vup, orc, n, B, cells):
+    """Every bin by its mass, the posterior's sum over the cells of a bin, and
+    the normalisers, on maps of 16 384 pdfs."""
+    K, m = 16384, 160
+    mm, b = _matrix(vup, orc, n, B)
+    mu, sg = _gaussians(n, LO, HI, K, cells, B)
+    P, Z = vup.propagate(mm, mu, sg)
+    at = np.random.default_rng(1).choice(K, size=m, replace=False)
+    p = _cpu(P)[at].astype(np.float64)
+    po, zo = orc.propagate(n, LO, HI, b, B, mu[at], sg[at])
+    has = po > 0
+    err = np.abs(p - po)[has] / po[has]
+    _say(f"[small bins {n} B={B} {cells}] smallest {po[has].min():.1e}, largest error over the "
+         f"bar {(err / (REL + ABS / po[has])).max():.2f}")
+    assert (po[has] < 1e-7).any()
+    assert (err <= REL + ABS / po[has]).all()
+    np.testing.assert_allclose(_cpu(Z)[at], zo, rtol=1e-7)
+    post, _ = vup.posterior(mm, mu, sg, None, at, P, Z)
+    post = _cpu(post).astype(np.float64)
+    for t in range(m):
+        s = np.bincount(b, weights=post[t], minlength=B)[has[t]]
+        # (its factors are FP32: a few units of 2^-24)
+        assert (np.abs(s - 1.0) <= 2 * (REL + ABS / po[t][has[t]]) + 2.0 ** -20).all(), t
+
+
+def test_narrow_pdfs(vup, orc):
+    """Deviations far below a cell, next to wide ones and outside the grid."""
+    n, B, K = (131, 200), 40, 16384
+    mm, b = _matrix(vup, orc, n, B)
+    rng = np.random.default_rng(6)
+    h = np.array([6.0 / 131, 6.0 / 200])
+    mu = rng.uniform(-3 - 3 * h, 3 + 3 * h, size=(K, 1, 2))
+    sg = 10.0 ** rng.uniform(-4, 1, size=(K, 1, 2)) * h
+    sg[:2000] = 10.0 ** rng.uniform(-12, -4, size=(2000, 1, 2)) * h
+    P, Z = vup.propagate(mm, mu, sg, n_sigma=6.0)
+    P, Z = _cpu(P).astype(np.float64), _cpu(Z)[:, 0]
+    Po, Zo = orc.propagate(n, LO, HI, b, B, mu, sg, n_sigma=6.0)
+    Zo = Zo[:, 0]
+    # densities below FP64's range have no P: vup_propagate's rows, bit for bit
+    # (none at the end of the range are compared)
+    ok = (Zo > 1e-290) | (Po == 0).all(1)
+    none = np.nonzero((Zo == 0) & ~ok)[0][:8000]
+    assert ok.sum() > 3000 and len(none) > 3000
+    Pn, _ = vup.propagate(mm, mu[none], sg[none], n_sigma=6.0)
+    assert np.array_equal(P[none], _cpu(Pn), equal_nan=True) and np.isnan(P[none]).any()
+    assert np.isfinite(P[ok]).all() and np.abs(P - Po)[ok].sum(1).max() <= 2e-5
+    np.testing.assert_allclose(Z[ok], Zo[ok], rtol=2e-6)
+    w = _cpu(vup.windows(mm.grid, mu, sg, n_sigma=6.0))[:, 0]
+    one = (w[..., 0] == w[..., 1]).all(1) & ok & (Zo > 0)  # a single cell
+    assert one.sum() > 50 and (P[one].max(1) == 1.0).all() and (P[one].sum(1) == 1.0).all()
+
+
+def test_workspace_sets_the_passes(vup, orc):
+    """Any workspace between the least and the full one gives the same results:
+    the pdfs are taken in passes, and by vup_propagate's kernel when a pass
+    would be too small."""
+    n, B, K = (190, 150), 300, 70001
+    mm, _ = _matrix(vup, orc, n, B)
+    mu, sg = _gaussians(n, LO, HI, K, (0.5, 20.0), 9)
+    sg[17] = -1.0
+    mu, sg = torch.from_numpy(mu).to(DEV), torch.from_numpy(sg).to(DEV)
+    d, lib = vup._dists(mu, sg, None, 4.0), vup.lib()
+    m, dd = ctypes.byref(mm.mm), ctypes.byref(d)
+    least = lib.vup_propagate_tiled_workspace_bytes(m, dd, 0)
+    full = lib.vup_propagate_tiled_full_workspace_bytes(m, dd, 0)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def call(nb):
+        ws = torch.full((nb,), 0xA5, dtype=torch.uint8, device=DEV)
+        P = torch.full((K, B), -7.0, device=DEV)
+        Z = torch.full((K, 1), -7.0, dtype=torch.float64, device=DEV)
+        assert lib.vup_propagate_tiled(m, dd, 0, ptr(ws), nb, ptr(P), ptr(Z), stream) == 0
+        return P.nan_to_num(-1.0), Z.nan_to_num(-1.0)
+
+    ref = call(full)
+    assert least < full
+    for share in (2, 4):  # (three and four passes: the least part does not shrink with K)
+        P, Z = call(least + (full - least) // share)
+        assert torch.equal(P, ref[0]) and torch.equal(Z, ref[1]), share
+    P, Z = call(least)
+    Pp, Zp = vup.propagate(mm, mu[:5000], sg[:5000])  # the per-pdf kernel
+    assert torch.equal(P[:5000], Pp.nan_to_num(-1.0)) and torch.equal(Z[:5000], Zp.nan_to_num(-1.0))
+    assert (P - ref[0]).abs().sum(1).max() <= 4e-5
