@@ -216,6 +216,8 @@ struct BinArgs {
   long long rows;
   long long nblk;
   int chunk;          // padded positions per chunk
+  PtBlock* tblocks;   // the tiles' blocks (2-D grids)
+  int ntblocks;
 };
 
 // bin index of y: largest b < B with e[b] <= y, when e[0] <= y <= e[B]
@@ -259,6 +261,8 @@ __global__ __launch_bounds__(256) void k_bin(BinArgs a) {
     // the counters start here (cells without a bin and runs follow)
     if (threadIdx.x < 8) a.counters[threadIdx.x] = threadIdx.x == kCntBadEdges && bad ? 1ull : 0ull;
   }
+  for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < a.ntblocks; t += a.nblk * 256)
+    a.tblocks[t].done = 0;
   const double span = e[a.B] - e[0];
   const double inv = span > 0.0 && span < 1e300 && span > 1e-280 ? a.B / span : 0.0;
   const long long base = (long long)blockIdx.x * a.chunk;
@@ -806,6 +810,11 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
   a.rows = mm.rows;
   a.nblk = L.nblk;
   a.chunk = L.chunk;
+  const int nbx = (mm.grid.n[1] + kPX - 1) / kPX, nby = (mm.grid.n[0] + kPL - 1) / kPL;
+  if (mm.grid.ndim == 2) {
+    a.tblocks = reinterpret_cast<PtBlock*>(ws + L.off_tblocks);
+    a.ntblocks = nbx * nby;
+  }
   const size_t lds = (size_t)(mm.B + 1) * 8 + (size_t)(mm.B + 1) * 4;
   hipLaunchKernelGGL(k_bin, dim3((unsigned)L.nblk), dim3(256), lds, s, a);
   FormArgs m{};
@@ -847,7 +856,6 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
   m.swaves = (size_t)(mm.B + 1) * 16 <= 65536 ? 4 : 2;
   size_t fill_lds = (size_t)(mm.B + 1) * 4 * m.swaves;
   if (mm.grid.ndim == 2) {
-    const int nbx = (mm.grid.n[1] + kPX - 1) / kPX, nby = (mm.grid.n[0] + kPL - 1) / kPL;
     m.ent.n[0] = mm.grid.n[0];
     m.ent.n[1] = mm.grid.n[1];
     m.ent.pitch = mm.pitch;
@@ -856,9 +864,10 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
     m.ent.binmap = a.binmap;
     m.ent.entries = reinterpret_cast<uint2*>(ws + L.off_tents);
     m.ent.chunks = reinterpret_cast<PtChunk*>(ws + L.off_tchunks);
-    m.ent.blocks = reinterpret_cast<PtBlock*>(ws + L.off_tblocks);
+    m.ent.blocks = a.tblocks;
     m.ent.cap = mm.N / 10;
     m.ent.counter = a.counters + kCntTiles;
+    m.ent.passes = a.counters + kCntPasses;
     m.entblocks = nbx * nby;
     if (fill_lds < sizeof(TileEntriesLds)) fill_lds = sizeof(TileEntriesLds);
   }

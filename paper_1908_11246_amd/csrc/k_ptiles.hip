@@ -39,21 +39,23 @@
 // cells, the bins' relative errors are (median, 99th percentile; per-pdf form
 // in brackets) 2e-8, 5e-8 (6e-8, 1e-6) above a thousandth of the mass, 3e-8,
 // 2e-6 (5e-5, 2e-3) around 1e-6, 7e-7, 1e-5 (6e-3, 9e-2) around 1e-10; columns'
-// L1 error 2.1e-8 (6.4e-8). Sums in 32 bits of the whole mass, two workgroups'
-// worth of LDS less, lost bins below 1e-10 altogether.
+// L1 error 2.1e-8 (6.4e-8). Sums in 32 bits of the whole mass lost bins below
+// 1e-10 altogether.
 //
 // Measured, 65 536 pdfs on 1024^2 cells, 256 bins, deviations of 8.5 to 85
-// cells: 1.23 ms per-pdf form, 0.79 ms here (k_pt_main 0.72; k_pt_prep, which
-// clears the sums, k_pt_scan and k_pt_final 0.02, 0.016 and 0.034). k_pt_main
-// issues VALU on 0.73 of the cycles with three waves per SIMD (per entry and
-// wave 17 VALU instructions, four 4-byte reads and one atomic). With 32-bit
-// sums (four waves per SIMD) it took 0.58 ms, 0.66 with three; running sums
-// over the four rows instead of exact steps (13 VALU instructions) 0.75.
-// Integer sums with conversions and FP32 FMAs took 24 VALU instructions per
-// entry; one wave per workgroup with its own tables left two waves per SIMD
-// (2.2 ms); entries through scalar loads were slower (the wait for a scalar
-// load is a wait for the LDS too), and so was looking for the tile's pdfs
-// inside the sweep.
+// cells: 1.23 ms per-pdf form, 0.72 ms here (k_pt_main 0.65; k_pt_prep, which
+// clears the sums, k_pt_scan and k_pt_final 0.022, 0.017 and 0.035). k_pt_main
+// is bound by VALU issue and the LDS pipe together (per entry and wave 17 VALU
+// instructions, eight of them FP64, four 4-byte reads and one atomic). With
+// 32-bit sums (13 VALU instructions) 0.58 ms. Workgroups of four waves and 66
+// bins, three to a CU: 0.77 ms, 0.57 instead of 0.42 where tiles need two
+// passes; 42 bins, four to a CU, 0.84; an entry's mass rounded once, after a
+// chain of multiply-adds from 0, 0.02 ms more, slots read one entry at a time
+// 0.01. Integer sums with conversions and FP32 FMAs took 24 VALU instructions
+// per entry; one wave per workgroup with its own tables left two waves per
+// SIMD (2.2 ms); entries through scalar loads were slower (the wait for a
+// scalar load is a wait for the LDS too), and so was looking for the tile's
+// pdfs inside the sweep.
 #include <hip/hip_runtime.h>
 
 #include "k_ptiles.hpp"
@@ -217,9 +219,9 @@ __global__ __launch_bounds__(kPScan) void k_pt_scan(PtArgs a) {
   const int part = blockIdx.x % a.parts, tile = blockIdx.x / a.parts;
   const int tx = tile % a.ntx, ty = tile / a.ntx;
   const int kbeg = part * kPPart, kend = (int)min((long long)kbeg + kPPart, a.K);
-  // the entries are used when they fit and their row steps are at most three
-  // times the model matrix's runs; otherwise the per-pdf kernel takes all pdfs
-  const bool use = tiles_pay(a.counters[kCntTiles], a.counters[kCntRuns]);
+  // otherwise the per-pdf kernel takes all pdfs
+  const bool use = tiles_pay(a.counters[kCntTiles], a.counters[kCntRuns], a.counters[kCntPasses],
+                             a.ntx * a.nty);
   if (tile == 0 && !use) {
     for (int k = kbeg + threadIdx.x; k < kend; k += kPScan) {
       a.rec[k].scale = 0.0;
@@ -281,23 +283,25 @@ __global__ __launch_bounds__(kPScan) void k_pt_scan(PtArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// per batch (64 pdfs of a tile's lists, one per lane): four waves; wave w forms the prefix sums of columns 16 w .. 16 w + 15 and sweeps
-// rows 16 w .. 16 w + 15
+// per batch (64 pdfs of a tile's lists, one per lane): eight waves; wave w
+// forms the prefix sums of columns 8 w .. 8 w + 7 and sweeps rows 16 w ..
+// 16 w + 15. Eight waves share the sums of 120 bins: two workgroups to a CU,
+// four waves per SIMD, and tiles of 120 bins in one pass.
 // ---------------------------------------------------------------------------
 // bit j of a lane's mask as 0 or -1
 __device__ __forceinline__ uint32_t bit_mask(uint32_t m, int j) {
   return (uint32_t)__builtin_amdgcn_sbfe((int)m, j, 1);
 }
 
-constexpr int kPWaves = 4;
+constexpr int kPWaves = 8;
 constexpr int kPWCols = kPX / kPWaves;            // columns of a wave
 constexpr int kPWRows = kPY / kPWaves;            // rows of a wave
 constexpr int kPWCh = kPWRows / kPR;              // chunks of a wave
-static_assert(kPWCh * kPWaves == 2 * kPCh && kPWRows == 32, "a wave's rows lie in one block");
+static_assert(kPWCh * kPWaves == 2 * kPCh && kPL % kPWRows == 0, "a wave's rows lie in one block");
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-__global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
+__global__ __launch_bounds__(64 * kPWaves, 4) void k_pt_main(PtArgs a) {
   __shared__ uint32_t sG[(kPX + 1) * 64];        // [column][lane] prefix sums
   // [slot][lane xor slot] sums; slot kPSlots: cells without a bin, then a
   // slot for bins outside the pass
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
   uint32_t two52 = 0x43300000u;  // high word of 2^52 (kept from the optimiser)
   asm("" : "+v"(two52));
   if (w == 0) sG[lane] = 0u;
-  for (int i = threadIdx.x; i < (kPSlots + 2) * 64; i += 256) sH[i] = 0ull;
+  for (int i = threadIdx.x; i < (kPSlots + 2) * 64; i += 64 * kPWaves) sH[i] = 0ull;
   // workgroups take batches until none is left: the first by their index, the
   // next ones from a counter
   const int nbatches = a.state[0];
@@ -326,10 +330,10 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
   const int tx = tile % a.ntx, ty = tile / a.ntx;
   const int c0 = tx * kPX + kPWCols * w, r0 = ty * kPY + kPWRows * w;  // of the wave
   // the wave's chunks and the tile's bins (its two blocks of lists)
-  const int ly = 2 * ty + w / 2;
+  const int ly = 2 * ty + w / (kPWaves / 2);
   const long long blk = (long long)ly * a.ntx + tx;
   const bool have = ly < a.nly;
-  const PtChunk* cs = a.chunks + blk * kPCh + kPWCh * (w & 1);
+  const PtChunk* cs = a.chunks + blk * kPCh + kPWCh * (w & (kPWaves / 2 - 1));
   int tmn, tmx, tnone;
   {
     const PtBlock b0 = a.blocks[(long long)(2 * ty) * a.ntx + tx];
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
     }
   }
   // passes over the tile's bins, kPSlots at a time (nearly always one)
-  const int passes = tmx >= tmn ? (tmx - tmn) / kPSlots + 1 : 1;
+  const int passes = tile_passes(tmn, tmx);
 
   {
     PtRec r;
@@ -388,16 +392,14 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
     const double ty0 = fma((double)(r0 - r.lo[0]), dt0, r.t0[0]);
     const double tx0 = fma((double)(c0 - r.lo[1]), dt1, r.t0[1]);
     // The recurrences start at the wave's first row and column, which may lie
-    // outside the window, n dt deviations further out (15 columns, 31 rows, or
-    // 15 when the rows start again half way). A factor e^-36 below the largest
-    // is below the units used; one that counts has a start above e^-620 while
-    // n dt <= 16 and e <= kPMaxOff, so it is never lost to underflow. Pdfs
-    // narrower than a cell, and means far outside the grid, have each of their
-    // factors formed by itself (with the t of k_pt_prep, so that the largest is
-    // exactly 1 however narrow the pdf).
+    // outside the window, n dt deviations further out (7 columns, 15 rows). A
+    // factor e^-36 below the largest is below the units used; one that counts
+    // has a start above e^-620 while n dt <= 16 and e <= kPMaxOff, so it is
+    // never lost to underflow. Pdfs narrower than a cell, and means far outside
+    // the grid, have each of their factors formed by itself (with the t of
+    // k_pt_prep, so that the largest is exactly 1 however narrow the pdf).
     const bool direct = __any(valid && (fmax(dt0, dt1) > kPMaxStep || fmax(r.e[0], r.e[1]) > kPMaxOff));
-    const bool restart = __any(valid && (kPWRows - 1) * dt0 > 16.0);
-    static_assert((kPWCols - 1) * kPMaxStep <= 16 && (kPWRows / 2 - 1) * kPMaxStep <= 16, "range");
+    static_assert((kPWCols - 1) * kPMaxStep <= 16 && (kPWRows - 1) * kPMaxStep <= 16, "range");
     uint32_t G[kPWCols], sum = 0u;
     if (!direct) {
       double g = unit * pt_exp(pt_arg(ec, tx0));
@@ -438,27 +440,32 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
     for (int ps = 0; ps < passes; ++ps) {
       const int base = tmn + ps * kPSlots;
       if (have) {
+        // the wave's chunks of the pass: those with bins of it (cells without a
+        // bin go to the first)
+        uint32_t todo = (1u << kPWCh) - 1u;
+        if (passes > 1) {
+          const PtChunk c = cs[lane & (kPWCh - 1)];
+          todo &= (uint32_t)__ballot((c.mn < base + kPSlots && c.mx >= base) || (ps == 0 && c.mn < 0));
+        }
         double g = S0 * pt_exp(pt_arg(r.e[0], ty0) + er);
         double q = pt_exp(fmin(-(ty0 + 0.5 * dt0) * dt0, 700.0));
         const double qq = pt_exp(-dt0 * dt0);
         uint32_t rm = rmask;
-        // buffers of prefix sums as doubles 2^52 + G: only the low words change
-        u32x2 A[2 * kPR], Bf[2 * kPR], Cf[2 * kPR];
+        // buffers of prefix sums as doubles 2^52 + G (only the low words change):
+        // two pairs of entries, and the last entry's
+        u32x2 A[2 * kPR], Bf[2 * kPR], Cf[kPR];
 #pragma unroll
         for (int j = 0; j < 2 * kPR; ++j) {
-          A[j][0] = Bf[j][0] = Cf[j][0] = 0u;
-          A[j][1] = Bf[j][1] = Cf[j][1] = two52;
+          A[j][0] = Bf[j][0] = 0u;
+          A[j][1] = Bf[j][1] = two52;
         }
+#pragma unroll
+        for (int j = 0; j < kPR; ++j) Cf[j][1] = two52;
         int cn = __builtin_amdgcn_readfirstlane(cs[0].n);
         const uint2* ev = a.entries + __builtin_amdgcn_readfirstlane(cs[0].first);
         uint2 ent = ev[lane];  // (there are 64 entries more than the model matrix has)
 #pragma unroll 1
         for (int ch = 0; ch < kPWCh; ++ch) {
-          if (restart && ch == kPWCh / 2) {
-            const double t = fma((double)(kPWRows / 2), dt0, ty0);
-            g = S0 * pt_exp(pt_arg(r.e[0], t) + er);
-            q = pt_exp(fmin(-(t + 0.5 * dt0) * dt0, 700.0));
-          }
           double gx[kPR];
 #pragma unroll
           for (int i = 0; i < kPR; ++i) {
@@ -487,11 +494,10 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
             ev = a.entries + __builtin_amdgcn_readfirstlane(cs[ch + 1].first);
             ent = ev[lane];
           }
-          if (!any) continue;  // no pdf of the batch has these rows
-          // every row stands at column 0 (the second half of Cf is what the
-          // first entry's sums are subtracted from)
+          if (!any || !(todo >> ch & 1u)) continue;  // no pdf of the batch has these rows
+          // every row stands at column 0
 #pragma unroll
-          for (int j = 0; j < kPR; ++j) Cf[kPR + j][0] = 0u;
+          for (int j = 0; j < kPR; ++j) Cf[j][0] = 0u;
           for (int f = 0; f < n; f += 64) {
             const int m = min(64, n - f);  // even
             uint2 e = first;
@@ -502,6 +508,10 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
               if (b == (uint32_t)kPNoBin ? ps > 0 : b - (uint32_t)base >= (uint32_t)kPSlots)
                 slot = slot_code(kPSlots + 1);
             }
+            // the slots of an even entry and the next one (row_shl:1; a pair lies in a
+            // row of 16 lanes)
+            const uint32_t slots =
+                slot | (uint32_t)__builtin_amdgcn_mov_dpp((int)slot, 0x101, 0xF, 0xF, true) << 16;
             auto load = [&](int i, u32x2 (&o)[2 * kPR]) {
               const uint32_t cols[2] = {(uint32_t)__builtin_amdgcn_readlane((int)e.x, i),
                                         (uint32_t)__builtin_amdgcn_readlane((int)e.x, i + 1)};
@@ -515,50 +525,43 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
                 o[4 * u + 3][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel3));
               }
             };
-            // the bin's mass: the rows' steps of G (exact differences) times
-            // their factors, rounded once to the fixed point
-            auto add = [&](int i, const u32x2 (&o)[2 * kPR], const u32x2 (&before)[2 * kPR]) {
+            // 2^52 and the bin's mass: the rows' steps of G (exact differences)
+            // times their factors, each rounded to the fixed point
+            auto add = [&](int i, const u32x2 (&o)[2 * kPR]) {
+              const uint32_t both = (uint32_t)__builtin_amdgcn_readlane((int)slots, i);
 #pragma unroll
               for (int u = 0; u < 2; ++u) {
-                double sum = 0.0;
+                double sum = 4503599627370496.0;
 #pragma unroll
                 for (int j = 0; j < kPR; ++j) {
                   const double d = __builtin_bit_cast(double, o[4 * u + j]) -
-                                   __builtin_bit_cast(double, u ? o[j] : before[kPR + j]);
-                  sum = j ? __builtin_fma(gx[j], d, sum) : gx[0] * d;
+                                   __builtin_bit_cast(double, u ? o[j] : Cf[j]);
+                  sum = __builtin_fma(gx[j], d, sum);
                 }
-                const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)slot, i + u);
+                const uint32_t at = u ? both >> 16 : both & 0xFFFFu;
                 unsigned long long* h = reinterpret_cast<unsigned long long*>(
                     reinterpret_cast<char*>(sH) + (at ^ lane8));
                 __hip_atomic_fetch_add(
-                    h, (unsigned long long)__double_as_longlong(sum + 4503599627370496.0),
+                    h, (unsigned long long)__double_as_longlong(sum),
                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
               }
             };
-            // two entries at a time, the reads of the next two in flight; three
-            // buffers, as the sums of one pair are subtracted from the next one's
+            // two entries at a time, the reads of the next two in flight
             load(0, A);
-            for (int i = 0;; i += 6) {
-              if (i + 2 < m) load(i + 2, Bf);
+            for (int i = 0;; i += 4) {
+              const bool more = i + 2 < m, more2 = i + 4 < m;
+              if (more) load(i + 2, Bf);
               __builtin_amdgcn_sched_barrier(0);
-              add(i, A, Cf);
-              if (i + 2 >= m) {
+              add(i, A);
 #pragma unroll
-                for (int j = 0; j < kPR; ++j) Cf[kPR + j] = A[kPR + j];
-                break;
-              }
-              if (i + 4 < m) load(i + 4, Cf);
+              for (int j = 0; j < kPR; ++j) Cf[j][0] = A[kPR + j][0];
+              if (!more) break;
+              if (more2) load(i + 4, A);
               __builtin_amdgcn_sched_barrier(0);
-              add(i + 2, Bf, A);
-              if (i + 4 >= m) {
+              add(i + 2, Bf);
 #pragma unroll
-                for (int j = 0; j < kPR; ++j) Cf[kPR + j] = Bf[kPR + j];
-                break;
-              }
-              if (i + 6 < m) load(i + 6, A);
-              __builtin_amdgcn_sched_barrier(0);
-              add(i + 4, Cf, Bf);
-              if (i + 6 >= m) break;
+              for (int j = 0; j < kPR; ++j) Cf[j][0] = Bf[kPR + j][0];
+              if (!more2) break;
             }
           }
         }
@@ -571,26 +574,23 @@ __global__ __launch_bounds__(256, 3) void k_pt_main(PtArgs a) {
       const int span = min(tmx - base + 1, kPSlots);
       const int b0 = base % kPSlots;  // slot of the pass's first bin
       auto give = [&](int b, int p) {  // bin base + b of pdf p
+        if (b >= span) return;
         const int s = b0 + b < kPSlots ? b0 + b : b0 + b - kPSlots;
         const int at = s * 64 + (p ^ (s & 63));
         const unsigned long long v = sH[at] & kPSum;
         const uint32_t o = sOff[p] + (uint32_t)(base + b);
         sH[at] = 0ull;
-        if (v && b < span) __hip_atomic_fetch_add(&a.acc[o], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v) __hip_atomic_fetch_add(&a.acc[o], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
       if (span > 32) {
+        for (int b = 0; b < span; b += 64) {
 #pragma unroll 4
-        for (int i = 0; i < 16; ++i) give(lane, 4 * i + w);
-        if (span > 64) {
-          // the last slots: 16 lanes a pdf
-          static_assert(kPSlots <= 80, "16 slots after the first 64");
-          if (64 + (lane & 15) < span)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) give(64 + (lane & 15), 16 * i + 4 * w + (lane >> 4));
+          for (int i = 0; i < 64 / kPWaves; ++i) give(b + lane, kPWaves * i + w);
         }
       } else {
 #pragma unroll 4
-        for (int i = 0; i < 8; ++i) give(lane & 31, 8 * i + 2 * w + (lane >> 5));
+        for (int i = 0; i < 32 / kPWaves; ++i)
+          give(lane & 31, 2 * kPWaves * i + 2 * w + (lane >> 5));
       }
       if (ps + 1 < passes) __syncthreads();
     }
@@ -681,11 +681,11 @@ long long pt_blocks(const vup_mm& mm) {
   return (long long)pt_div(mm.grid.n[1], kPX) * pt_div(mm.grid.n[0], kPL);
 }
 
-long long pt_tiles(const vup_mm& mm) {
-  return (long long)pt_div(mm.grid.n[1], kPX) * pt_div(mm.grid.n[0], kPY);
-}
-
 }  // namespace
+
+long long tile_count(const vup_grid& g) {
+  return (long long)pt_div(g.n[1], kPX) * pt_div(g.n[0], kPY);
+}
 
 // 8 bytes per ten cells: the entries of model matrices with runs of three
 // cells or more; 64 more are read past the last
@@ -701,21 +701,21 @@ bool propagate_tiled_applies(const vup_mm& mm, const vup_dists& d, int prec) {
   if (mm.sweep != VUP_SWEEP_RUNS || !runs_allowed(mm) || mm.reserved == kTilesNot) return false;
   return d.K >= kPtMinK && d.K < (1ll << 24) && d.K * mm.B < (1ll << 30) && mm.N < (1ll << 28) &&
          pt_blocks(mm) <= kPMaxBlocks &&
-         pt_tiles(mm) * pt_div((int)d.K, kPPart) * kPPart <= kPMaxList;
+         tile_count(mm.grid) * pt_div((int)d.K, kPPart) * kPPart <= kPMaxList;
 }
 
 size_t propagate_tiled_ws_bytes(const vup_mm& mm, long long K) {
-  return pt_layout(pt_tiles(mm), K).acc + al256((size_t)K * 4);
+  return pt_layout(tile_count(mm.grid), K).acc + al256((size_t)K * 4);
 }
 
 size_t propagate_tiled_full_bytes(const vup_mm& mm, long long K) {
   const size_t least = propagate_tiled_ws_bytes(mm, K);
-  const size_t full = pt_pass_bytes(pt_tiles(mm), mm.B, pt_share(K, mm.B));
+  const size_t full = pt_pass_bytes(tile_count(mm.grid), mm.B, pt_share(K, mm.B));
   return full > least ? full : least;
 }
 
 long long propagate_tiled_pass(const vup_mm& mm, long long K, size_t ws_bytes) {
-  const long long ntiles = pt_tiles(mm);
+  const long long ntiles = tile_count(mm.grid);
   long long kg = pt_share(K, mm.B);
   for (long long passes = (K + kg - 1) / kg; kg >= kPtMinK; ++passes, kg = (K + passes - 1) / passes)
     if (pt_pass_bytes(ntiles, mm.B, kg) <= ws_bytes) return kg;
@@ -746,7 +746,7 @@ static hipError_t launch_pass(const vup_mm& mm, const vup_dists& d, void* ws, fl
   a.ntx = pt_div(a.n[1], kPX);
   a.nty = pt_div(a.n[0], kPY);
   a.nly = pt_div(a.n[0], kPL);
-  const long long ntiles = pt_tiles(mm);
+  const long long ntiles = tile_count(mm.grid);
   a.parts = (int)((d.K + kPPart - 1) / kPPart);
   const PtLayout L = pt_layout(ntiles, d.K);
   char* base = static_cast<char*>(ws);
@@ -763,8 +763,8 @@ static hipError_t launch_pass(const vup_mm& mm, const vup_dists& d, void* ws, fl
   const long long pb = (d.K + 255) / 256;
   hipLaunchKernelGGL(k_pt_prep, dim3((unsigned)(pb > 2048 ? pb : 2048)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_pt_scan, dim3((unsigned)(ntiles * a.parts)), dim3(kPScan), 0, s, a);
-  // as many workgroups as fit on the GPU (three per CU)
-  hipLaunchKernelGGL(k_pt_main, dim3(768), dim3(256), 0, s, a);
+  // as many workgroups as fit on the GPU (two per CU)
+  hipLaunchKernelGGL(k_pt_main, dim3(512), dim3(64 * kPWaves), 0, s, a);
   hipLaunchKernelGGL(k_pt_final, dim3((unsigned)((d.K + 3) / 4)), dim3(256), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

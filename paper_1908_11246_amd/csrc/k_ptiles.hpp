@@ -15,14 +15,14 @@ constexpr int kPL = 64;            // rows of a block of entries
 constexpr int kPR = 4;             // rows of a chunk
 constexpr int kPCh = kPL / kPR;    // chunks of a block
 constexpr int kPEnt = 128;         // entries a chunk may have
-constexpr int kPSlots = 66;        // bins a pass over a tile covers: three workgroups' LDS fit on a CU
+constexpr int kPSlots = 120;       // bins a pass over a tile covers: two workgroups' LDS fit on a CU
 constexpr int kPNoBin = 0xFFFF;    // entry of cells without a bin
 
 // one chunk's entries
 struct PtChunk {
   uint32_t first;  // index of the first entry
   uint32_t n;      // entries (an even number)
-  int mn, mx;      // lowest and highest bin (mn > mx: none)
+  int mn, mx;      // lowest and highest bin (mn > mx: none); mn -1: cells without one
 };
 static_assert(sizeof(PtChunk) == 16, "chunk layout");
 
@@ -30,7 +30,7 @@ static_assert(sizeof(PtChunk) == 16, "chunk layout");
 struct PtBlock {
   int mn, mx;
   int none;        // it has cells without a bin
-  int pad;
+  int done;        // of a tile's two blocks, in the first one: how many are built
 };
 static_assert(sizeof(PtBlock) == 16, "block layout");
 
@@ -44,6 +44,7 @@ struct PtEntArgs {
   PtBlock* blocks;              // [blocks]
   long long cap;                // entries there is room for
   unsigned long long* counter;  // entries; kPUnfit and more: they do not fit
+  unsigned long long* passes;   // passes over all tiles
 };
 constexpr unsigned long long kPUnfit = 1ull << 40;
 
@@ -54,6 +55,11 @@ __device__ __forceinline__ uint32_t slot_code(int s) {
   return (uint32_t)s * 512u + ((uint32_t)s & 63u) * 8u;
 }
 static_assert((kPSlots + 2) * 512 <= 65536, "16 bits of an entry");
+
+// passes over a tile of bins mn .. mx
+__device__ __forceinline__ int tile_passes(int mn, int mx) {
+  return mx >= mn ? (mx - mn) / kPSlots + 1 : 1;
+}
 
 template <int CTRL>
 __device__ __forceinline__ int quad(int v) {
@@ -210,7 +216,7 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
       const int slot = b == kPNoBin ? kPSlots : b % kPSlots;
       if (room) a.entries[b0 + first + i] = make_uint2(sh.cols[rule][q][i], (uint32_t)b | slot_code(slot) << 16);
       if (b == kPNoBin) {
-        hasnone = 1;
+        if (i < sh.count[rule][q]) hasnone = 1;  // (not the entry that makes the list even)
       } else {
         mn = min(mn, b);
         mx = max(mx, b);
@@ -223,7 +229,7 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
     hasnone = __any(hasnone) ? 1 : 0;
     if (lane == 0) {
       a.chunks[(long long)block * kPCh + q] =
-          PtChunk{room ? (uint32_t)(b0 + first) : 0u, room ? (uint32_t)m : 0u, mn, mx};
+          PtChunk{room ? (uint32_t)(b0 + first) : 0u, room ? (uint32_t)m : 0u, hasnone ? -1 : mn, mx};
       sh.range[q][0] = mn;
       sh.range[q][1] = mx;
       sh.range[q][2] = hasnone;
@@ -231,13 +237,29 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    PtBlock t = {0x7fff, -1, 0, 0};
+    int mn = 0x7fff, mx = -1, none = 0;
     for (int q = 0; q < kPCh; ++q) {
-      t.mn = min(t.mn, sh.range[q][0]);
-      t.mx = max(t.mx, sh.range[q][1]);
-      t.none |= sh.range[q][2];
+      mn = min(mn, sh.range[q][0]);
+      mx = max(mx, sh.range[q][1]);
+      none |= sh.range[q][2];
     }
-    a.blocks[block] = t;
+    PtBlock* t = a.blocks + block;
+    t->mn = mn;
+    t->mx = mx;
+    t->none = none;
+    // the tile's passes, by whichever of its two blocks comes second
+    const int other = tx + (ty ^ 1) * a.ntx;
+    bool count = true;
+    if ((ty ^ 1) * kPL < a.n[0]) {
+      __threadfence();
+      count = atomicAdd(&a.blocks[min(block, other)].done, 1) == 1;
+      if (count) {
+        __threadfence();
+        mn = min(mn, __hip_atomic_load(&a.blocks[other].mn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        mx = max(mx, __hip_atomic_load(&a.blocks[other].mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      }
+    }
+    if (count) atomicAdd(a.passes, (unsigned long long)tile_passes(mn, mx));
   }
 }
 

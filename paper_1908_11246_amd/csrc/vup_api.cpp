@@ -379,7 +379,9 @@ int vup_set_sweep_mode(vup_mm* mm, int32_t mode, void* stream) {
     const int64_t nruns = cnt[vup::kCntRuns];
     const bool runs = vup::runs_allowed(*mm) && nruns > 0 && nruns * vup::kRunMinLength <= mm->N;
     mm->reserved = mm->grid.ndim == 2 && vup::tiles_pay((unsigned long long)cnt[vup::kCntTiles],
-                                                        (unsigned long long)nruns)
+                                                        (unsigned long long)nruns,
+                                                        (unsigned long long)cnt[vup::kCntPasses],
+                                                        vup::tile_count(mm->grid))
                        ? vup::kTilesPay
                        : vup::kTilesNot;
     mode = runs ? VUP_SWEEP_RUNS : VUP_SWEEP_CELLS;

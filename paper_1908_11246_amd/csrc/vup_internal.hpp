@@ -63,7 +63,9 @@ constexpr long long kPtMinK = 16384;
 // propagation pays for the model matrix, or not (0: not looked, the device
 // decides on each call)
 constexpr int kTilesPay = 1, kTilesNot = 2;
-// bytes of the tiled propagation's entries of a 2-D model matrix
+// tiles of a 2-D grid, and bytes of the tiled propagation's entries of its model
+// matrix
+long long tile_count(const vup_grid& g);
 void tile_entry_sizes(const vup_grid& g, size_t* ents, size_t* chunks, size_t* blocks);
 bool propagate_tiled_applies(const vup_mm& mm, const vup_dists& d, int prec);
 size_t propagate_tiled_ws_bytes(const vup_mm& mm, long long K);

@@ -286,3 +286,44 @@ def test_workspace_sets_the_passes(vup, orc):
     Pp, Zp = vup.propagate(mm, mu[:5000], sg[:5000])  # the per-pdf kernel
     assert torch.equal(P[:5000], Pp.nan_to_num(-1.0)) and torch.equal(Z[:5000], Zp.nan_to_num(-1.0))
     assert (P - ref[0]).abs().sum(1).max() <= 4e-5
+
+
+def test_tiles_of_several_passes(vup, orc):
+    """Tiles whose bins need up to three passes, with cells without a bin among
+    them, next to tiles of one; and the count of passes that decides on the tiles."""
+    n, K, m = (1408, 256), 16384, 160
+    rows = np.r_[np.full(128, 2.3), np.full(n[0] - 128, 0.25)].cumsum()
+    f = (rows[:, None] + 0.2 * np.arange(n[1])[None, :]).ravel()
+    f[::977] = np.nan
+    e = np.arange(40.0, np.nanmax(f) + 1.0)  # the first 40 bins' cells have none
+    B = len(e) - 1
+    b = orc.bins(f, e)
+    g = vup.make_grid(n, LO, HI)
+    mm = vup.build_model_matrix(g, torch.from_numpy(f).to(DEV), torch.from_numpy(e).to(DEV))
+    passes = 0
+    for y in range(0, n[0], 128):
+        for x in range(0, n[1], 64):
+            q = b.reshape(n)[y:y + 128, x:x + 64]
+            q = q[q >= 0]
+            passes += (q.max() - q.min()) // 120 + 1
+    tiles = (n[0] // 128) * (n[1] // 64)
+    assert int(mm._view(mm.mm.off_counters, torch.int64, 8)[5]) == passes > tiles
+    assert mm.sweep == "runs" and mm.mm.reserved == 1  # the tiles pay
+    mu, sg = _gaussians(n, LO, HI, K, (1.0, 40.0), 11)
+    mu[:K // 2, 0, 0] = np.random.default_rng(2).uniform(-3.0, -2.4, size=K // 2)  # the steep rows
+    P, Z = vup.propagate(mm, mu, sg)
+    P, reached = _cpu(P), _reached(vup, mm, b, mu, sg, B)
+    assert (P[~reached] == 0).all()
+    at = np.random.default_rng(3).choice(K // 2, size=m, replace=False)
+    po, zo = orc.propagate(n, LO, HI, b, B, mu[at], sg[at])
+    p, has = P[at].astype(np.float64), po > 0
+    err = np.abs(p - po)[has] / po[has]
+    _say(f"[several passes] {passes} of {tiles} tiles, largest error over the bar "
+         f"{(err / (REL + ABS / po[has])).max():.2f}")
+    assert (err <= REL + ABS / po[has]).all()
+    np.testing.assert_allclose(_cpu(Z)[at], zo, rtol=1e-7)
+    # too many passes: found not to pay
+    f = np.add.outer(2.3 * np.arange(256.0), 0.2 * np.arange(256.0)).ravel()
+    mm = vup.build_model_matrix(vup.make_grid((256, 256), LO, HI), torch.from_numpy(f).to(DEV),
+                                torch.arange(0.0, f.max() + 1.0, dtype=torch.float64, device=DEV))
+    assert mm.sweep == "runs" and mm.mm.reserved == 2
