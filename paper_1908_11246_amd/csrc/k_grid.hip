@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void k_bin(BinArgs a) {
     if (threadIdx.x < 8) a.counters[threadIdx.x] = threadIdx.x == kCntBadEdges && bad ? 1ull : 0ull;
   }
   for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < a.ntblocks; t += a.nblk * 256)
-    a.tblocks[t].done = 0;
+    a.tblocks[t].both = 0ull;
   const double span = e[a.B] - e[0];
   const double inv = span > 0.0 && span < 1e300 && span > 1e-280 ? a.B / span : 0.0;
   const long long base = (long long)blockIdx.x * a.chunk;
@@ -867,7 +867,7 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
     m.ent.blocks = a.tblocks;
     m.ent.cap = mm.N / 10;
     m.ent.counter = a.counters + kCntTiles;
-    m.ent.passes = a.counters + kCntPasses;
+    m.ent.extra = a.counters + kCntPasses;
     m.entblocks = nbx * nby;
     if (fill_lds < sizeof(TileEntriesLds)) fill_lds = sizeof(TileEntriesLds);
   }

@@ -7,6 +7,8 @@
 
 #include <cstdint>
 
+#include "../../include/vup.h"
+
 namespace vup {
 namespace {
 
@@ -28,9 +30,9 @@ static_assert(sizeof(PtChunk) == 16, "chunk layout");
 
 // a block's bins
 struct PtBlock {
-  int mn, mx;
-  int none;        // it has cells without a bin
-  int done;        // of a tile's two blocks, in the first one: how many are built
+  int16_t mn, mx;
+  int none;                 // it has cells without a bin
+  unsigned long long both;  // in the first of a tile's two blocks: the bins of those built
 };
 static_assert(sizeof(PtBlock) == 16, "block layout");
 
@@ -44,7 +46,7 @@ struct PtEntArgs {
   PtBlock* blocks;              // [blocks]
   long long cap;                // entries there is room for
   unsigned long long* counter;  // entries; kPUnfit and more: they do not fit
-  unsigned long long* passes;   // passes over all tiles
+  unsigned long long* extra;    // passes over the tiles past the first over each
 };
 constexpr unsigned long long kPUnfit = 1ull << 40;
 
@@ -111,6 +113,8 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
   const int ncol = min(kPX, a.n[1] - c0), nrow = min(kPL, a.n[0] - r0);
   const int none = 4 * a.B;
   if (threadIdx.x < kPCh) sh.best[threadIdx.x] = kPEnt + 1;
+  // (an old value will do)
+  if (threadIdx.x == 0) sh.base = (long long)*a.counter;
   // bit c of a row's mask: a run starts at column c > 0
   {
     int v[kPL / 4];
@@ -130,6 +134,7 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
     }
   }
   __syncthreads();
+  if (sh.base >= (long long)kPUnfit) return;  // no use of any (uniform)
   const unsigned long long mask = sh.starts[lane];
   const int end = lane < nrow ? ncol : 0;
   const int ch = lane >> 2, li = lane & 3;
@@ -244,22 +249,25 @@ __device__ __forceinline__ void tile_entries(const PtEntArgs& a, int block, Tile
       none |= sh.range[q][2];
     }
     PtBlock* t = a.blocks + block;
-    t->mn = mn;
-    t->mx = mx;
+    t->mn = (int16_t)mn;
+    t->mx = (int16_t)mx;
     t->none = none;
-    // the tile's passes, by whichever of its two blocks comes second
-    const int other = tx + (ty ^ 1) * a.ntx;
+    // the tile's passes, by whichever of its two blocks comes second: the bins
+    // go round with the count, a half of the word each, so no fence is needed
+    // (with fences vup_bin took 371 us at 4096^2 cells, 230 so)
     bool count = true;
     if ((ty ^ 1) * kPL < a.n[0]) {
-      __threadfence();
-      count = atomicAdd(&a.blocks[min(block, other)].done, 1) == 1;
-      if (count) {
-        __threadfence();
-        mn = min(mn, __hip_atomic_load(&a.blocks[other].mn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        mx = max(mx, __hip_atomic_load(&a.blocks[other].mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      }
+      static_assert(VUP_MAX_BINS < (1 << 14), "14 bits a bin");
+      const uint32_t mine = 1u << 30 | (uint32_t)(mx + 1) << 14 | (uint32_t)min(mn, 0x3fff);
+      const unsigned long long was =
+          atomicAdd(&a.blocks[tx + (ty & ~1) * a.ntx].both, (unsigned long long)mine << (32 * (ty & 1)));
+      const uint32_t other = (uint32_t)(was >> (32 * (~ty & 1)));
+      count = other != 0u;
+      mn = min(mn, (int)(other & 0x3fffu));
+      mx = max(mx, (int)(other >> 14 & 0xffffu) - 1);
     }
-    if (count) atomicAdd(a.passes, (unsigned long long)tile_passes(mn, mx));
+    const int extra = tile_passes(mn, mx) - 1;
+    if (count && extra > 0) atomicAdd(a.extra, (unsigned long long)extra);
   }
 }
 

@@ -30,8 +30,8 @@ constexpr int kMaxBinsPerThread = (VUP_MAX_BINS + 1 + kThreads - 1) / kThreads;
 // [4]: number of runs of equal bin along the fastest axis (set by vup_bin,
 // not cleared by vup_counters); the propagation uses the run form when the
 // mean run length is at least kRunMinLength cells.
-// [5], [7]: passes over the tiles and entries of the tiled propagation (2-D
-// grids, set by vup_bin); [6]: sweep mode (VUP_SWEEP_*).
+// [5], [7]: passes over the tiles past the first, and entries, of the tiled
+// propagation (2-D grids, set by vup_bin); [6]: sweep mode (VUP_SWEEP_*).
 enum Counter {
   kCntOutside = 0,
   kCntBadEdges = 1,
@@ -44,17 +44,17 @@ enum Counter {
 };
 constexpr int kRunMinLength = 3;
 // The tiled propagation pays for a model matrix of so many entries (of four
-// row steps each; a count past its room is far larger), runs, and passes over
-// so many tiles. Against the per-pdf kernel, 16 384 and 65 536 pdfs, deviations
+// row steps each; a count past its room is far larger), runs, and passes past
+// the first over so many tiles. Against the per-pdf kernel, 16 384 and 65 536 pdfs, deviations
 // of 4 to 85 cells, 512^2 cells and 5 to 20 cells to a run: at 2.9 row steps to
 // a run 1.2 to 2.0 times as fast, at 1.2 steps 1.5 to 2.3 times. A second pass
 // over a tile forms the row factors and hands its bins' sums on once more: with
 // 1.06 passes to a tile (300 x 1100 cells, 200 bins) 1.3 to 1.8 times, with 1.39
 // (420 bins) 0.82 to 1.16, with two or more (rising by a bin a row) 0.5 to 1.1.
 __host__ __device__ inline bool tiles_pay(unsigned long long entries, unsigned long long nruns,
-                                          unsigned long long passes, long long tiles) {
+                                          unsigned long long extra, long long tiles) {
   return entries < (1ull << 40) && 4 * entries <= 3 * nruns &&
-         5 * passes <= 6 * (unsigned long long)tiles;
+         5 * extra <= (unsigned long long)tiles;
 }
 
 // grid + bin-map description passed by value to every sweep kernel
