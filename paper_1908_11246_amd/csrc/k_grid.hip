@@ -180,12 +180,13 @@ hipError_t launch_uniform_edges(const double* f, int64_t N, int B, double* edges
   long long blocks = (N + 2047) / 2048;  // eight values per thread
   if (blocks > 1024) blocks = 1024;
   if (blocks < 1) blocks = 1;
-  // the edges themselves hold the workgroups' pairs when there is room for a
-  // quarter of the workgroups: two launches and no atomics (at 2^20 cells and
-  // 256 bins 7.5 + 2.8 us; 1.4 + 9.4 + 2.4 us with atomics and one value in
-  // flight per thread)
+  // the edges themselves hold the workgroups' pairs when there is room for
+  // enough of them: two launches and no atomics (at 2^20 cells and 256 bins 7.5
+  // + 2.8 us; 1.4 + 9.4 + 2.4 us with atomics and one value in flight per
+  // thread). A workgroup takes about 0.47 ns a value: with 128 of them, 2^21
+  // values take 12 us (19 with atomics), 2^22 18.5 (20), 2^24 69 (34)
   long long parts = (B + 1) / 2 < blocks ? (B + 1) / 2 : blocks;
-  if (4 * parts >= blocks || parts >= 128) {
+  if (parts >= 320 || N <= 20480 * parts) {
     hipLaunchKernelGGL(k_minmax<true>, dim3((unsigned)parts), dim3(256), 0, s, f, (long long)N, e,
                        B);
   } else {
