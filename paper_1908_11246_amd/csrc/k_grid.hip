@@ -436,6 +436,9 @@ hipError_t launch_windows(const vup_grid& g, const vup_dists& d, int32_t* win, h
 // ---------------------------------------------------------------------------
 // workspace layout
 // ---------------------------------------------------------------------------
+// 32-cell blocks of a row segment: a wave counts and fills a segment's runs
+constexpr int kSegBlocks = 64;
+
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 bool ws_layout(const vup_grid& g, int B, WsLayout* out) {
@@ -453,6 +456,7 @@ bool ws_layout(const vup_grid& g, int B, WsLayout* out) {
     L.chunk *= 2;
   L.nblk = (padded + L.chunk - 1) / L.chunk;
   const long long rowblocks = L.rows * (L.pitch / 32);
+  L.nseg = (L.pitch / 32 + kSegBlocks - 1) / kSegBlocks;
   size_t o = 0;
   L.off_edges = o;
   o = align256(o + (size_t)(B + 1) * 8);
@@ -473,6 +477,8 @@ bool ws_layout(const vup_grid& g, int B, WsLayout* out) {
   o = align256(o + scratch);
   L.off_tsum = o;  // tile sums of the prefix scans
   o = align256(o + (size_t)(scan_tiles((long long)(scratch / 4)) + 1) * 8);
+  L.off_segs = o;  // rows of several segments: the segments' first runs
+  if (L.nseg > 1) o = align256(o + (size_t)(L.rows * L.nseg + 1) * 4);
   L.off_counters = o;
   o = align256(o + 8 * 8);
   L.off_runs = o;
@@ -514,15 +520,19 @@ struct FormArgs {
   int chunk;
   // runs
   uint32_t* runs;
-  int* rowptr;         // [rows + 1]: runs and a terminator per row, then their scan
+  int* rowptr;         // [rows + 1] first run of each row
+  // [rows * nseg + 1]: runs of each row segment of 64 blocks, with the terminator
+  // in the row's last, then their scan; rowptr itself for rows of one segment
+  int* segs;
+  int nseg;
   uint16_t* runidx;
   unsigned long long* counters;
   long long rows;
   int nL, pitch, nb;   // nb 32-cell blocks per row
-  int group;           // lanes per row: a power of two, at least nb up to 64
+  int group;           // lanes per segment: a power of two, at least nb up to 64
   int rowblocks;       // workgroups of the run part
   int swaves;          // chunks per workgroup of the scatter
-  int scan_rows;       // k_offsets scans the row pointers too
+  int scan_segs;       // k_offsets scans the segments too
   // entries of the tiled propagation (2-D grids)
   int entblocks;       // workgroups of that part
   PtEntArgs ent;
@@ -570,7 +580,7 @@ __device__ __forceinline__ uint32_t run_starts(const Block32& b, int q, int nL) 
 }
 
 // Workgroups 0 .. B: bin b's chunk counts, scanned (exclusive) in place, and
-// its total. The others: `group` lanes per row count the row's runs.
+// its total. The others: `group` lanes per row segment count its runs.
 __global__ __launch_bounds__(256) void k_count(FormArgs a) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if ((int)blockIdx.x <= a.B) {
@@ -609,13 +619,15 @@ __global__ __launch_bounds__(256) void k_count(FormArgs a) {
     return;
   }
   const long long t = (long long)(blockIdx.x - a.B - 1) * 256 + threadIdx.x;
-  const long long r = t / a.group;
-  if (r >= a.rows) return;  // whole groups
+  const long long sg = t / a.group;
+  if (sg >= a.rows * a.nseg) return;  // whole groups
+  const long long r = sg / a.nseg;
+  const int part = (int)(sg - r * a.nseg);
+  const int q = part * kSegBlocks + (int)(t % a.group);
   int cnt = 0;
-  for (int q = (int)(t % a.group); q < a.nb; q += a.group)
-    cnt += __popc(run_starts(load_block32(a.binmap + r * a.pitch, q), q, a.nL));
+  if (q < a.nb) cnt = __popc(run_starts(load_block32(a.binmap + r * a.pitch, q), q, a.nL));
   for (int o = a.group >> 1; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if (t % a.group == 0) a.rowptr[r] = cnt + 1;  // the row's terminator
+  if (t % a.group == 0) a.segs[sg] = cnt + (part == a.nseg - 1 ? 1 : 0);
 }
 
 // exclusive scan of n values by one workgroup of 1024 threads; returns the sum
@@ -651,8 +663,8 @@ __device__ __forceinline__ long long scan_block(const T* in, T* out, long long n
   return carry;
 }
 
-// workgroup 0: CSR row starts from the bins' counts; workgroup 1: run row
-// pointers. The run and outside counts go to the counters.
+// workgroup 0: CSR row starts from the bins' counts; workgroup 1: the row
+// segments' first runs. The run and outside counts go to the counters.
 __global__ __launch_bounds__(1024) void k_offsets(FormArgs a) {
   __shared__ long long wsum[16];
   if (blockIdx.x == 0) {
@@ -660,11 +672,12 @@ __global__ __launch_bounds__(1024) void k_offsets(FormArgs a) {
     if (threadIdx.x == 0) a.counters[kCntOutside] = (unsigned long long)a.counts[a.B];
   } else {
     long long total;
-    if (a.scan_rows) {
-      total = scan_block(a.rowptr, a.rowptr, a.rows, wsum);
-      if (threadIdx.x == 0) a.rowptr[a.rows] = (int)total;
+    const long long n = a.rows * a.nseg;
+    if (a.scan_segs) {
+      total = scan_block(a.segs, a.segs, n, wsum);
+      if (threadIdx.x == 0) a.segs[n] = (int)total;
     } else {
-      total = a.rowptr[a.rows];  // scanned by launch_scan_excl
+      total = a.segs[n];  // scanned by launch_scan_excl
     }
     if (threadIdx.x == 0) a.counters[kCntRuns] = (unsigned long long)(total - a.rows);
   }
@@ -751,7 +764,7 @@ __device__ __forceinline__ void fill_runs(const FormArgs& a, long long r, int q,
 }
 
 // the first workgroups build the tiled propagation's entries, the next fill
-// the runs (`group` lanes per row), the others scatter (a wave per chunk)
+// the runs (`group` lanes per row segment), the others scatter (a wave per chunk)
 __global__ __launch_bounds__(256) void k_fill(FormArgs a) {
   // [waves][B+1] running positions of the chunks, or TileEntriesLds
   extern __shared__ __align__(16) int pos[];
@@ -767,28 +780,29 @@ __global__ __launch_bounds__(256) void k_fill(FormArgs a) {
     return;
   }
   const long long t = (long long)block * 256 + threadIdx.x;
-  const long long r = t / a.group;
-  const bool in = r < a.rows;
-  const int g = lane & (a.group - 1);
-  const int rowstart = in ? a.rowptr[r] : 0;
-  int carry = rowstart;
-  for (int q0 = 0; q0 < a.nb; q0 += a.group) {
-    const int q = q0 + g;
-    Block32 blk = {};
-    uint32_t starts = 0;
-    if (in && q < a.nb) {
-      blk = load_block32(a.binmap + r * a.pitch, q);
-      starts = run_starts(blk, q, a.nL);
-    }
-    const int cnt = __popc(starts);
-    int incl = cnt;
-    for (int o = 1; o < a.group; o <<= 1) {
-      const int x = __shfl_up(incl, o, a.group);
-      if (g >= o) incl += x;
-    }
-    if (in && q < a.nb) fill_runs(a, r, q, blk, starts, rowstart, carry + incl - cnt);
-    carry += __shfl(incl, a.group - 1, a.group);
+  const long long sg = t / a.group;
+  const bool in = sg < a.rows * a.nseg;
+  const long long r = in ? sg / a.nseg : 0;
+  const int part = (int)(sg - r * a.nseg);
+  const int g = lane & (a.group - 1), q = part * kSegBlocks + g;
+  const int rowstart = in ? a.segs[r * a.nseg] : 0;
+  if (in && a.nseg > 1 && g == 0) {
+    if (part == 0) a.rowptr[r] = rowstart;
+    if (sg == a.rows * a.nseg - 1) a.rowptr[a.rows] = a.segs[sg + 1];
   }
+  Block32 blk = {};
+  uint32_t starts = 0;
+  if (in && q < a.nb) {
+    blk = load_block32(a.binmap + r * a.pitch, q);
+    starts = run_starts(blk, q, a.nL);
+  }
+  const int cnt = __popc(starts);
+  int incl = cnt;
+  for (int o = 1; o < a.group; o <<= 1) {
+    const int x = __shfl_up(incl, o, a.group);
+    if (g >= o) incl += x;
+  }
+  if (in && q < a.nb) fill_runs(a, r, q, blk, starts, rowstart, a.segs[sg] + incl - cnt);
 }
 
 hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, int32_t* bin,
@@ -837,18 +851,21 @@ hipError_t launch_bin(const vup_mm& mm, const double* f, const double* edges, in
   m.nb = a.pitch / 32;
   m.group = 1;
   while (m.group < m.nb && m.group < 64) m.group *= 2;
-  // one workgroup scans up to 16384 row pointers in four steps (12.4 us, 3.1
-  // us at 1024 rows); more take three launches over many workgroups (13.8 us
+  // one workgroup scans up to 16384 segments in four steps (12.4 us, 3.1
+  // us at 1024 rows of one); more take three launches over many workgroups (13.8 us
   // at 110592 rows), where one workgroup would take 27 steps
-  m.scan_rows = mm.rows <= 16384;
-  const long long rowthreads = mm.rows * m.group;
+  const long long nsegs = mm.rows * L.nseg;
+  m.nseg = L.nseg;
+  m.segs = L.nseg > 1 ? reinterpret_cast<int*>(ws + L.off_segs) : m.rowptr;
+  m.scan_segs = nsegs <= 16384;
+  const long long rowthreads = nsegs * m.group;
   hipLaunchKernelGGL(k_count, dim3((unsigned)(mm.B + 1 + (rowthreads + 255) / 256)), dim3(256), 0,
                      s, m);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  if (!m.scan_rows) {
-    err = launch_scan_excl(m.rowptr, mm.rows, reinterpret_cast<long long*>(ws + L.off_tsum),
-                           m.rowptr + mm.rows, s);
+  if (!m.scan_segs) {
+    err = launch_scan_excl(m.segs, nsegs, reinterpret_cast<long long*>(ws + L.off_tsum),
+                           m.segs + nsegs, s);
     if (err != hipSuccess) return err;
   }
   hipLaunchKernelGGL(k_offsets, dim3(2), dim3(1024), 0, s, m);

@@ -105,8 +105,9 @@ struct WsLayout {
   int64_t rows;
   int64_t nblk;  // chunks of the bin sort
   int chunk;     // padded positions per chunk
+  int nseg;      // segments of a row, in the construction of the runs
   size_t off_edges, off_binmap, off_f32, off_counts, off_offsets, off_perm, off_scratch,
-      off_counters, off_runs, off_rowptr, off_runidx, off_tsum, off_tents, off_tchunks, off_tblocks,
+      off_counters, off_runs, off_rowptr, off_runidx, off_tsum, off_segs, off_tents, off_tchunks, off_tblocks,
       bytes;
 };
 bool ws_layout(const vup_grid& g, int B, WsLayout* out);
