@@ -55,6 +55,7 @@ struct PostArgs {
   float* post;
   double* mean;
   int gtab;                 // the fastest-axis factor table fits in LDS
+  int vec;                  // rows of post take float4 stores (n_L % 4 == 0, aligned)
   double rn[4];             // 1 / n_d, for the index arithmetic of the means
 };
 
@@ -63,10 +64,13 @@ struct PostArgs {
 // factor f[c][b] = pi_c / (Z_c P[k][b]) of every bin (0 where P is 0), so a
 // cell costs its fastest-axis factor and one multiply-add per component.
 // Per row: the product of the other axes' factors (uniform over the row).
+// COLS: a thread keeps the fastest-axis factors of its columns and goes down
+// the workgroup's rows (with float4 stores only); otherwise the factors are
+// formed once per workgroup, side by side, and kept in LDS.
 constexpr int kPostRows = 64;  // rows whose factors are kept at once
-template <bool VEC>
+template <bool COLS>
 __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
-  extern __shared__ float sfb[];  // [C][B + 1], then (!VEC, when it fits) fastest-axis factors [C][n_L]
+  extern __shared__ float sfb[];  // [C][B + 1], then (!COLS, when it fits) fastest-axis factors [C][n_L]
   __shared__ int swin[VUP_MAX_COMP][VUP_MAX_DIM][2];
   __shared__ double smu[VUP_MAX_COMP][VUP_MAX_DIM], srs[VUP_MAX_COMP][VUP_MAX_DIM];
   __shared__ int sm[VUP_MAX_COMP][VUP_MAX_DIM];  // the factors' scale exponents
@@ -118,7 +122,7 @@ __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
   // the fastest-axis factor of every column inside each component's window,
   // shared by all rows of this distribution
   float* gtab = sfb + C * (B + 1);
-  if (!VEC && a.gtab && kok) {
+  if (!COLS && a.gtab && kok) {
     // only the window's columns: the cells read no others
     for (int c = 0; c < C; ++c) {
       const int wlo = swin[c][D - 1][0], whi = swin[c][D - 1][1];
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
     }
     return v;
   };
-  if constexpr (VEC) {
+  if constexpr (COLS) {
     // A thread owns four columns: their fastest-axis factors stay in registers
     // (-1 outside the component's window) while it goes down the workgroup's
     // rows, four rows at once (four 8-byte loads of bin codes, four 16-byte
@@ -274,6 +278,27 @@ __global__ __launch_bounds__(256) void k_posterior(PostArgs a) {
                   make_float4(o[0], o[1], o[2], o[3]);
           }
         }
+      }
+    }
+  } else if (a.vec) {
+    // four columns per thread: one 8-byte load of bin codes, one 16-byte store
+    const float fill = bad ? __builtin_nanf("") : 0.0f;
+    for (int r = blockIdx.x; r < a.rows; r += gridDim.x) {
+      RowInfo ri;
+      row_info(r, ri);
+      const uint16_t* brow = a.binmap + (long long)r * a.pitch;
+      float4* prow4 = reinterpret_cast<float4*>(post + (long long)r * nL);
+      for (int c4 = threadIdx.x; c4 < (nL >> 2); c4 += blockDim.x) {
+        const int col0 = 4 * c4;
+        float4 o = make_float4(fill, fill, fill, fill);
+        if (!bad && col0 + 3 >= ri.ulo && col0 <= ri.uhi) {
+          const uint2 cw = *reinterpret_cast<const uint2*>(brow + col0);
+          o.x = cell(ri, col0, cw.x & 0xFFFFu);
+          o.y = cell(ri, col0 + 1, cw.x >> 16);
+          o.z = cell(ri, col0 + 2, cw.y & 0xFFFFu);
+          o.w = cell(ri, col0 + 3, cw.y >> 16);
+        }
+        prow4[c4] = o;
       }
     }
   } else {
@@ -712,17 +737,28 @@ hipError_t launch_posterior(const vup_mm& mm, const vup_dists& d, int64_t n_sel,
   a.mean = mean;
   for (int x = 0; x < 4; ++x) a.rn[x] = 1.0 / a.n[x];
   const int nL = a.n[a.ndim - 1];
-  const bool vec = (nL % 4 == 0) && ((reinterpret_cast<uintptr_t>(post) & 15u) == 0);
+  a.vec = (nL % 4 == 0) && ((reinterpret_cast<uintptr_t>(post) & 15u) == 0);
   a.gtab = (size_t)d.ncomp * (mm.B + 1 + nL) * sizeof(float) <= 65536 ? 1 : 0;
-  const size_t lds = (size_t)d.ncomp * (mm.B + 1 + (a.gtab && !vec ? nL : 0)) * sizeof(float);
   // about 32 rows per workgroup, so the per-bin factors and the factor table
   // are set up rarely, but at least 2048 workgroups in all while rows last
-  long long gx = (mm.rows + 31) / 32;
-  const long long want = (2048 + n_sel - 1) / n_sel;
-  if (gx < want) gx = want < mm.rows ? want : mm.rows;
-  gx = gx < 1 ? 1 : (gx > 4096 ? 4096 : gx);
+  // (4096 where they have few rows each)
+  auto groups = [&](long long least) {
+    long long gx = (mm.rows + 31) / 32;
+    const long long want = (least + n_sel - 1) / n_sel;
+    if (gx < want) gx = want < mm.rows ? want : mm.rows;
+    return gx < 1 ? 1 : (gx > 4096 ? 4096 : gx);
+  };
+  long long gx = groups(2048);
+  // Factors in registers pay from two rows per workgroup on (1000^2 cells: 4
+  // locations, two rows, 18.5 -> 16.0 us, 64 locations, 31 rows, 77 -> 40; 20^4
+  // cells, 8 locations 101 -> 16). A thread forms its four columns' factors one
+  // after the other, which a single row does not pay back: 1000^2 cells, one
+  // location 7.8 us side by side, 9.1 so; 10 x 4096, 64 locations 9.2 and 13.8.
+  const bool cols = a.vec && mm.rows >= 2 * gx;
+  if (!cols) gx = groups(4096);
+  const size_t lds = (size_t)d.ncomp * (mm.B + 1 + (a.gtab && !cols ? nL : 0)) * sizeof(float);
   const dim3 grid((unsigned)gx, (unsigned)n_sel);
-  if (vec) hipLaunchKernelGGL(k_posterior<true>, grid, dim3(256), lds, s, a);
+  if (cols) hipLaunchKernelGGL(k_posterior<true>, grid, dim3(256), lds, s, a);
   else hipLaunchKernelGGL(k_posterior<false>, grid, dim3(256), lds, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !mean) return e;
