@@ -15,7 +15,7 @@
 //                     post x_d, over the part of the model matrix's
 //                     compressed-by-bin cell list inside the window's index
 //                     range (fixed summation order)
-//   k_posterior_mean  the same for grids whose factor tables do not fit, one
+//   k_posterior_mean  the same where factor tables do not fit or pay, one
 //                     wave per (t, b), reading post
 //
 // 64 of 256 locations, 1000^2 cells, 1000 bins: k_posterior writes 256 MB in
@@ -765,19 +765,24 @@ hipError_t launch_posterior(const vup_mm& mm, const vup_dists& d, int64_t n_sel,
   size_t tab = 0;
   for (int x = 0; x < a.ndim; ++x) tab += (size_t)a.n[x];
   tab *= d.ncomp * sizeof(float);
-  // tables up to 32 KB leave four workgroups to a CU (64 locations, 1000^2
-  // cells: 49 us, 133 us without tables)
-  if (tab <= 32768) {
-    // bins per workgroup: about 4096 workgroups, but a bin for each of a
-    // workgroup's sixteen groups of lanes to share its tables (64 locations,
-    // 1000^2 cells, 1000 bins, the whole call: 16 bins 91 us, 32 bins 99, 64
-    // bins 112)
-    // a quarter of a wave per bin fills the chip from 16 384 bins on (same
-    // size: 49 us, 93 us with a wave per bin); fewer bins take a wave each
-    const bool narrow = n_sel * mm.B >= 16384;
-    long long per = (n_sel * mm.B + 4095) / 4096;
-    if (per < 16) per = 16;
-    if (per > 256) per = 256;
+  // Tables up to 32 KB leave four workgroups to a CU. A quarter of a wave per
+  // bin fills the chip from 16 384 bins on, 16 bins to a workgroup, one for each
+  // of its groups of lanes, so that they share its tables (64 locations, 1000^2
+  // cells, 1000 bins, the kernel: 48 us, 56 with 32 bins, 69 with 64, 93 with a
+  // wave per bin, 131 reading post), more bins once there are 4096 workgroups.
+  // Fewer bins take a wave each, four to a workgroup while there are fewer than
+  // 1024 (48^4 cells, 256 bins of one location, the call: 468 us reading post
+  // with a wave per bin, 582 from tables with 16 bins to a workgroup, 172 so).
+  // Long tables for few and small bins are not worth forming (8000 cells on one
+  // axis, 64 bins, the call: one location 14.4 us reading post, 17 from tables;
+  // four locations 21.7 and 20.0).
+  const long long bins = n_sel * mm.B;
+  const bool narrow = bins >= 16384;
+  long long per = narrow ? (bins + 4095) / 4096 : bins / 1024;
+  if (per < (narrow ? 16 : 4)) per = narrow ? 16 : 4;
+  if (per > 256) per = 256;
+  const long long entries = (long long)(tab / sizeof(float));
+  if (tab <= 32768 && (48 * bins >= entries || mm.N >= entries * mm.B)) {
     MeanDiv dv{};
     for (int x = 0; x < a.ndim; ++x) {
       int l = 0;

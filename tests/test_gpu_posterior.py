@@ -56,3 +56,30 @@ def test_posterior_by_rows_per_workgroup(vup, n, C, n_sel):
         pb = np.where(b >= 0, P[t][np.maximum(b, 0)], 0.0)
         want = np.where(pb > 0, want / np.where(pb > 0, pb, 1.0), 0.0)
         assert np.all(np.abs(post[t] - want) <= 16 * 2.0 ** -24 * want), t
+
+
+# from post (tables too long for few bins), from tables with four bins to a
+# workgroup, five, and sixteen with a quarter of a wave each
+@pytest.mark.parametrize("n,B,n_sel", [((8000,), 166, 1), ((8000,), 167, 1), ((60, 70), 31, 3),
+                                       ((60, 70), 1031, 5), ((60, 70), 1638, 10),
+                                       ((60, 70), 1639, 10)])
+def test_means_by_bins_per_workgroup(vup, n, B, n_sel):
+    """E[x | y in b] against the sums over the posterior of the same call: FP64,
+    so within 2 (m + 8) 2^-53 of the sum of the m terms' magnitudes."""
+    d = len(n)
+    rng = np.random.default_rng(B)
+    g = vup.make_grid(n, (-1.0,) * d, (1.5,) * d)
+    f = torch.from_numpy(rng.normal(size=int(np.prod(n)))).to(DEV)
+    mm = vup.build_model_matrix(g, f, vup.uniform_edges(f, B))
+    mu = rng.uniform(-1.0, 1.5, size=(n_sel, 1, d))
+    sg = rng.uniform(0.1, 0.5, size=(n_sel, 1, d))
+    P, Z = vup.propagate(mm, mu, sg)
+    post, mean = vup.posterior(mm, mu, sg, None, np.arange(n_sel), P, Z)
+    post, mean, b = _cpu(post).astype(np.float64), _cpu(mean), _cpu(mm.bin)
+    x = np.meshgrid(*[-1.0 + (np.arange(m) + 0.5) * (2.5 / m) for m in n], indexing="ij")
+    count = np.bincount(b, minlength=B)
+    for t in range(n_sel):
+        for i in range(d):
+            want = np.bincount(b, weights=post[t] * x[i].ravel(), minlength=B)
+            size = np.bincount(b, weights=post[t] * 2.5, minlength=B)
+            assert (np.abs(mean[t, :, i] - want) <= 2 * (count + 8) * 2.0 ** -53 * size).all(), t
