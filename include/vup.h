@@ -78,6 +78,7 @@ extern "C" {
 #define VUP_MAX_DY (1 << 24)  /* n_dy of vup_ipsa_matrix                         */
 #define VUP_MAX_LEVELS 16     /* quantile levels of vup_ipsa_fields              */
 #define VUP_MAX_MARGINAL_COLS (1 << 24)  /* row length n of vup_marginalize      */
+#define VUP_TILED_MIN_K 16384 /* fewest pdfs vup_propagate_tiled sweeps by tiles    */
 
 typedef struct vup_grid {
   int32_t ndim;      /* 1..4                                                   */
@@ -226,7 +227,7 @@ int vup_propagate(const vup_mm* mm, const vup_dists* d, int32_t precision, float
  * with vup_propagate's up to rounding (with more digits in bins of little mass)
  * and are bit-identical from run to run.
  * Applies to FP32 densities of single-component pdfs (ncomp == 1), K in
- * [16384, 2^24) and K B < 2^30, on 2-D grids of fewer than 2^28 cells and at
+ * [VUP_TILED_MIN_K, 2^24) and K B < 2^30, on 2-D grids of fewer than 2^28 cells and at
  * most 65 536 blocks of 64 x 64 cells whose sweep form is VUP_SWEEP_RUNS, with
  * at most 2^27 / 16384 tiles per 16384 pdfs (the lists of the pdfs that meet
  * each tile), unless VUP_SWEEP_AUTO found the model matrix's rows too unlike
@@ -239,7 +240,7 @@ int vup_propagate(const vup_mm* mm, const vup_dists* d, int32_t precision, float
  *   too small.
  *   The sums take 8 (B + 1) bytes per pdf more. With the second, full size all
  *   pdfs are swept at once, or in shares whose sums are about 256 MB; with less
- *   in more and smaller shares; and where they would fall below 16384 pdfs,
+ *   in more and smaller shares; and where they would fall below VUP_TILED_MIN_K,
  *   vup_propagate's kernel takes the call.
  * ------------------------------------------------------------------------ */
 size_t vup_propagate_tiled_workspace_bytes(const vup_mm* mm, const vup_dists* d,

@@ -34,6 +34,7 @@ STATUS = {-1: "VUP_EINVAL", -2: "VUP_ENODEV", -3: "VUP_EDEVICE", -4: "VUP_EUNSUP
           -5: "VUP_EWORKSPACE"}
 PRECISIONS = {"fp32": 0, "bf16": 1, "bf16x2": 2, "fp8e4m3": 3}
 MODELS = {"linear": 0, "sincos2": 1, "damped3": 2, "ring4": 3, "timing2": 4, "ipsa2": 5}
+TILED_MIN_K = 16384  # VUP_TILED_MIN_K: smaller calls do not ask for the tiles' workspace
 
 
 class VupError(RuntimeError):
@@ -336,9 +337,14 @@ def propagate(mm: ModelMatrix, mu, sigma, weight=None, precision: str = "fp32",
     lib = _load()
     mref, dref, prec = ctypes.byref(mm.mm), ctypes.byref(d), PRECISIONS[precision]
     # large sets of pdfs on 2-D grids are swept by tiles, which takes a workspace
-    nb = lib.vup_propagate_tiled_full_workspace_bytes(mref, dref, prec) if K >= 16384 else 0
+    nb = lib.vup_propagate_tiled_full_workspace_bytes(mref, dref, prec) if K >= TILED_MIN_K else 0
+    ws = None
     if nb:
-        ws = torch.empty(nb, dtype=torch.uint8, device=mm.device)
+        try:
+            ws = torch.empty(nb, dtype=torch.uint8, device=mm.device)
+        except torch.OutOfMemoryError:
+            pass  # vup_propagate needs none
+    if ws is not None:
         _check(lib.vup_propagate_tiled(mref, dref, prec, _ptr(ws), nb, _ptr(P), _ptr(Z),
                                        _vp(_stream())))
     else:

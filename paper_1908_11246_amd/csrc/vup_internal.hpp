@@ -52,13 +52,17 @@ hipError_t launch_windows(const vup_grid& g, const vup_dists& d, int32_t* win, h
 hipError_t launch_propagate(const vup_mm& mm, const vup_dists& d, int prec, float* P, double* Z,
                             hipStream_t s);
 // FP32 propagation of many single-component pdfs on a 2-D grid by tiles, one
-// pdf per lane (model matrices in the run form). From 16 384 pdfs on it was
-// faster than the per-pdf kernel at every size and deviation measured (sin/cos
-// model, deviations 0.05-0.5 and 0.05-0.1: 256^2 cells 110 -> 62 and 75 -> 52
-// us, 512^2 150 -> 74 and 83 -> 48, 1024^2 with 256 bins 375 -> 181 and 111 ->
-// 99); at 8100 pdfs narrow ones on 1024^2 cells take 76 us instead of 60, the
-// time of a few batches one after the other.
-constexpr long long kPtMinK = 16384;
+// pdf per lane (model matrices in the run form that tiles_pay). From 16 384
+// pdfs on it was faster than the per-pdf kernel at nearly every size, spread
+// and deviation measured (sin/cos model, 16 384 and 65 536 pdfs, deviations of 4
+// to 8 cells: 256^2 cells 87 -> 55 and 308 -> 117 us, 1024^2 86 -> 75 and 322 ->
+// 165, 4096^2 287 -> 110 and 1144 -> 319; of 8.5 to 85 cells: 1024^2 346 -> 218
+// and 1232 -> 719; of a tenth to half a cell: 65 536 pdfs 282 -> 181; models
+// rising evenly 1.04 to 2.3 times as fast, but for 0.96 and 0.99 where 100
+// columns leave a second column of tiles a third full). Fewer pdfs were not
+// measured against this form: narrow ones fill fewer batches than the chip
+// takes at once.
+constexpr long long kPtMinK = VUP_TILED_MIN_K;
 // vup_mm.reserved once vup_set_sweep_mode(AUTO) has looked: the tiled
 // propagation pays for the model matrix, or not (0: not looked, the device
 // decides on each call)

@@ -2,6 +2,7 @@
 include/vup.h declares, and rejects invalid arguments before touching a GPU.
 No compute call is made here (this runs on machines without a GPU)."""
 import ctypes
+import re
 import subprocess
 
 import pytest
@@ -426,3 +427,8 @@ def test_propagate_tiled_full_workspace(lib):
             lists = 84 * kg + 8 * -(-kg // 16384) * 33 * 1024
             assert full >= least
             assert full == least or lists + sums <= full <= lists + sums + 4096
+
+
+def test_tiled_min_k_matches_header():
+    txt = open(vup.HEADER).read()
+    assert int(re.search(r"#define VUP_TILED_MIN_K (\d+)", txt)[1]) == vup.TILED_MIN_K

@@ -328,3 +328,47 @@ def test_tiles_of_several_passes(vup, orc):
     mm = vup.build_model_matrix(vup.make_grid((256, 256), LO, HI), torch.from_numpy(f).to(DEV),
                                 torch.arange(0.0, f.max() + 1.0, dtype=torch.float64, device=DEV))
     assert mm.sweep == "runs" and mm.mm.reserved == 2
+
+
+def test_without_memory_for_the_workspace(vup, orc, monkeypatch):
+    """A call that finds no memory for the tiles' workspace is the per-pdf form's."""
+    mm, _ = _matrix(vup, orc, (190, 150), 20)
+    mu, sg = _gaussians((190, 150), LO, HI, 16384, (0.5, 20.0), 3)
+    ref = vup.propagate(mm, mu, sg)
+    empty = torch.empty
+
+    def no_bytes(*a, **kw):
+        if kw.get("dtype") is torch.uint8:
+            raise torch.OutOfMemoryError("none left")
+        return empty(*a, **kw)
+
+    monkeypatch.setattr(vup.torch, "empty", no_bytes)
+    P, Z = vup.propagate(mm, mu, sg)
+    monkeypatch.undo()
+    part = vup.propagate(mm, mu[:5000], sg[:5000])
+    assert torch.equal(P[:5000], part[0]) and torch.equal(Z[:5000], part[1])
+    assert (P - ref[0]).abs().sum(1).max() <= 4e-5
+
+
+def test_tiled_graph_capture(vup, orc):
+    """A captured tiled propagation, replayed over new pdfs with eager calls in
+    between, gives the eager results."""
+    n, B, K = (256, 256), 64, 16384
+    mm, _ = _matrix(vup, orc, n, B)
+    sets = [[torch.from_numpy(a).to(DEV) for a in _gaussians(n, LO, HI, K, (0.3, 30.0), s)]
+            for s in range(3)]
+    sets[1][1][100:200] = -1.0  # invalid ones among them
+    mu, sg = sets[0][0].clone(), sets[0][1].clone()
+    vup.propagate(mm, mu, sg)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        P, Z = vup.propagate(mm, mu, sg)
+    for i in (0, 1, 2, 1, 0):
+        mu.copy_(sets[i][0])
+        sg.copy_(sets[i][1])
+        ref = vup.propagate(mm, sets[i][0], sets[i][1])
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, r in zip((P, Z), ref):
+            assert torch.equal(a.nan_to_num(-1.0), r.nan_to_num(-1.0)), i
