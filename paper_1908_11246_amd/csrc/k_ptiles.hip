@@ -43,19 +43,21 @@
 // 1e-10 altogether.
 //
 // Measured, 65 536 pdfs on 1024^2 cells, 256 bins, deviations of 8.5 to 85
-// cells: 1.23 ms per-pdf form, 0.72 ms here (k_pt_main 0.65; k_pt_prep, which
+// cells: 1.23 ms per-pdf form, 0.71 ms here (k_pt_main 0.64; k_pt_prep, which
 // clears the sums, k_pt_scan and k_pt_final 0.022, 0.017 and 0.035). k_pt_main
-// is bound by VALU issue and the LDS pipe together (per entry and wave 17 VALU
-// instructions, eight of them FP64, four 4-byte reads and one atomic). With
-// 32-bit sums (13 VALU instructions) 0.58 ms. Workgroups of four waves and 66
+// is bound by the LDS pipe, with VALU issue close behind (per entry and wave
+// four 4-byte reads of 4 clocks and an atomic of 7, 15 VALU instructions, eight
+// of them FP64). With 32-bit sums (running sums over the four rows, 13 VALU
+// instructions, a 5-clock atomic) 0.58 ms. Workgroups of four waves and 66
 // bins, three to a CU: 0.77 ms, 0.57 instead of 0.42 where tiles need two
-// passes; 42 bins, four to a CU, 0.84; an entry's mass rounded once, after a
-// chain of multiply-adds from 0, 0.02 ms more, slots read one entry at a time
-// 0.01. Integer sums with conversions and FP32 FMAs took 24 VALU instructions
-// per entry; one wave per workgroup with its own tables left two waves per
-// SIMD (2.2 ms); entries through scalar loads were slower (the wait for a
-// scalar load is a wait for the LDS too), and so was looking for the tile's
-// pdfs inside the sweep.
+// passes; 42 bins, four to a CU, 0.84; two pairs of entries and a copy of the
+// last instead of the ring 0.72; an entry's mass rounded once, after a chain of
+// multiply-adds from 0, 0.02 ms more, slots read one entry at a time 0.01.
+// Integer sums with conversions and FP32 FMAs took 24 VALU instructions per
+// entry; one wave per workgroup with its own tables left two waves per SIMD
+// (2.2 ms); entries through scalar loads were slower (the wait for a scalar
+// load is a wait for the LDS too), and so was looking for the tile's pdfs
+// inside the sweep.
 #include <hip/hip_runtime.h>
 
 #include "k_ptiles.hpp"
@@ -451,16 +453,17 @@ __global__ __launch_bounds__(64 * kPWaves, 4) void k_pt_main(PtArgs a) {
         double q = pt_exp(fmin(-(ty0 + 0.5 * dt0) * dt0, 700.0));
         const double qq = pt_exp(-dt0 * dt0);
         uint32_t rm = rmask;
-        // buffers of prefix sums as doubles 2^52 + G (only the low words change):
-        // two pairs of entries, and the last entry's
-        u32x2 A[2 * kPR], Bf[2 * kPR], Cf[kPR];
+        // prefix sums as doubles 2^52 + G (only the low words change): a ring of
+        // four entries, this one, the next, and two on their way; the last one's
+        // place is free once this one's steps are formed
+        u32x2 Q[4][kPR];
 #pragma unroll
-        for (int j = 0; j < 2 * kPR; ++j) {
-          A[j][0] = Bf[j][0] = 0u;
-          A[j][1] = Bf[j][1] = two52;
-        }
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int j = 0; j < kPR; ++j) Cf[j][1] = two52;
+          for (int j = 0; j < kPR; ++j) {
+            Q[u][j][0] = 0u;
+            Q[u][j][1] = two52;
+          }
         int cn = __builtin_amdgcn_readfirstlane(cs[0].n);
         const uint2* ev = a.entries + __builtin_amdgcn_readfirstlane(cs[0].first);
         uint2 ent = ev[lane];  // (there are 64 entries more than the model matrix has)
@@ -497,7 +500,7 @@ __global__ __launch_bounds__(64 * kPWaves, 4) void k_pt_main(PtArgs a) {
           if (!any || !(todo >> ch & 1u)) continue;  // no pdf of the batch has these rows
           // every row stands at column 0
 #pragma unroll
-          for (int j = 0; j < kPR; ++j) Cf[j][0] = 0u;
+          for (int j = 0; j < kPR; ++j) Q[3][j][0] = 0u;
           for (int f = 0; f < n; f += 64) {
             const int m = min(64, n - f);  // even
             uint2 e = first;
@@ -512,55 +515,52 @@ __global__ __launch_bounds__(64 * kPWaves, 4) void k_pt_main(PtArgs a) {
             // row of 16 lanes)
             const uint32_t slots =
                 slot | (uint32_t)__builtin_amdgcn_mov_dpp((int)slot, 0x101, 0xF, 0xF, true) << 16;
-            auto load = [&](int i, u32x2 (&o)[2 * kPR]) {
-              const uint32_t cols[2] = {(uint32_t)__builtin_amdgcn_readlane((int)e.x, i),
-                                        (uint32_t)__builtin_amdgcn_readlane((int)e.x, i + 1)};
-#pragma unroll
-              for (int u = 0; u < 2; ++u) {
-                const uint32_t c = cols[u];
-                const char* p = reinterpret_cast<const char*>(sG);
-                o[4 * u][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel0));
-                o[4 * u + 1][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel1));
-                o[4 * u + 2][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel2));
-                o[4 * u + 3][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel3));
-              }
+            auto load = [&](int i, u32x2 (&o)[kPR]) {
+              const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)e.x, i);
+              const char* p = reinterpret_cast<const char*>(sG);
+              o[0][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel0));
+              o[1][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel1));
+              o[2][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel2));
+              o[3][0] = *reinterpret_cast<const uint32_t*>(p + __builtin_amdgcn_perm(c, lane4, sel3));
             };
             // 2^52 and the bin's mass: the rows' steps of G (exact differences)
             // times their factors, each rounded to the fixed point
-            auto add = [&](int i, const u32x2 (&o)[2 * kPR]) {
-              const uint32_t both = (uint32_t)__builtin_amdgcn_readlane((int)slots, i);
+            auto add = [&](uint32_t at, const u32x2 (&o)[kPR], const u32x2 (&before)[kPR]) {
+              double sum = 4503599627370496.0;
 #pragma unroll
-              for (int u = 0; u < 2; ++u) {
-                double sum = 4503599627370496.0;
-#pragma unroll
-                for (int j = 0; j < kPR; ++j) {
-                  const double d = __builtin_bit_cast(double, o[4 * u + j]) -
-                                   __builtin_bit_cast(double, u ? o[j] : Cf[j]);
-                  sum = __builtin_fma(gx[j], d, sum);
-                }
-                const uint32_t at = u ? both >> 16 : both & 0xFFFFu;
-                unsigned long long* h = reinterpret_cast<unsigned long long*>(
-                    reinterpret_cast<char*>(sH) + (at ^ lane8));
-                __hip_atomic_fetch_add(
-                    h, (unsigned long long)__double_as_longlong(sum),
-                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-              }
+              for (int j = 0; j < kPR; ++j)
+                sum = __builtin_fma(gx[j],
+                                    __builtin_bit_cast(double, o[j]) -
+                                        __builtin_bit_cast(double, before[j]),
+                                    sum);
+              unsigned long long* h = reinterpret_cast<unsigned long long*>(
+                  reinterpret_cast<char*>(sH) + (at ^ lane8));
+              __hip_atomic_fetch_add(h, (unsigned long long)__double_as_longlong(sum),
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             };
-            // two entries at a time, the reads of the next two in flight
-            load(0, A);
+            // (m is even; a whole segment ends on the ring's last place, where the
+            // next one looks for it)
+            load(0, Q[0]);
+            load(1, Q[1]);
             for (int i = 0;; i += 4) {
               const bool more = i + 2 < m, more2 = i + 4 < m;
-              if (more) load(i + 2, Bf);
+              uint32_t both = (uint32_t)__builtin_amdgcn_readlane((int)slots, i);
+              add(both & 0xFFFFu, Q[0], Q[3]);
+              if (more) {
+                load(i + 2, Q[2]);
+                load(i + 3, Q[3]);
+              }
               __builtin_amdgcn_sched_barrier(0);
-              add(i, A);
-#pragma unroll
-              for (int j = 0; j < kPR; ++j) Cf[j][0] = A[kPR + j][0];
+              add(both >> 16, Q[1], Q[0]);
               if (!more) break;
-              if (more2) load(i + 4, A);
+              both = (uint32_t)__builtin_amdgcn_readlane((int)slots, i + 2);
+              add(both & 0xFFFFu, Q[2], Q[1]);
+              if (more2) {
+                load(i + 4, Q[0]);
+                load(i + 5, Q[1]);
+              }
               __builtin_amdgcn_sched_barrier(0);
-              add(i + 2, Bf);
-#pragma unroll
-              for (int j = 0; j < kPR; ++j) Cf[j][0] = Bf[kPR + j][0];
+              add(both >> 16, Q[3], Q[2]);
               if (!more2) break;
             }
           }
