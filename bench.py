@@ -156,10 +156,10 @@ PRECISIONS = {"grid1024": ("fp32", "bf16", "bf16x2", "fp8e4m3"),
 CALIB_BYTES = 256 << 20
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 # LDS rates of the tiled propagation's operations, per CU and clock, at the
-# vendor clock: integer atomic adds free of conflicts (measured on this part
-# with a microbenchmark: 15 lanes per clock per CU) and the LDS bandwidth (128
-# bytes per clock per CU)
-LDS_ATOMIC_PEAK = 15 * 256 * 2.4e9
+# vendor clock: 64-bit integer atomic adds free of conflicts (measured on this
+# part with a microbenchmark: 8.3 lanes per clock per CU) and the LDS bandwidth
+# (128 bytes per clock per CU; 4-byte reads alone reached 51)
+LDS_ATOMIC_PEAK = 8.3 * 256 * 2.4e9
 LDS_BYTES_PEAK = 128 * 256 * 2.4e9
 
 
@@ -752,7 +752,7 @@ def main():
             "atomic_frac": R / 4 / t / LDS_ATOMIC_PEAK,
             "read_bytes_per_s": 4 * R / t, "read_peak_bytes_per_s": LDS_BYTES_PEAK,
             "read_frac": 4 * R / t / LDS_BYTES_PEAK,
-            "peaks": "conflict-free ds_add_u32 rate measured on this part (15 lanes/clk/CU) "
+            "peaks": "conflict-free ds_add_u64 rate measured on this part (8.3 lanes/clk/CU) "
                      "and LDS bandwidth (128 B/clk/CU), at 2.4 GHz"}
         log(f"[bench] run sums: {R:.3e} runs, LDS atomics "
             f"{rooflines['propagate']['lds']['atomic_frac']:.2f} and prefix-sum reads "

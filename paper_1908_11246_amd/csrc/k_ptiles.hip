@@ -46,9 +46,9 @@
 // cells: 1.23 ms per-pdf form, 0.71 ms here (k_pt_main 0.64; k_pt_prep, which
 // clears the sums, k_pt_scan and k_pt_final 0.022, 0.017 and 0.035). k_pt_main
 // is bound by the LDS pipe, with VALU issue close behind (per entry and wave
-// four 4-byte reads of 4 clocks and an atomic of 7, 15 VALU instructions, eight
-// of them FP64). With 32-bit sums (running sums over the four rows, 13 VALU
-// instructions, a 5-clock atomic) 0.58 ms. Workgroups of four waves and 66
+// four 4-byte reads of 5 clocks and an atomic of 8, measured alone, 15 VALU
+// instructions, eight of them FP64). With 32-bit sums (running sums over the
+// four rows, 13 VALU instructions, an atomic of 5.5 clocks) 0.58 ms. Workgroups of four waves and 66
 // bins, three to a CU: 0.77 ms, 0.57 instead of 0.42 where tiles need two
 // passes; 42 bins, four to a CU, 0.84; two pairs of entries and a copy of the
 // last instead of the ring 0.72; an entry's mass rounded once, after a chain of
