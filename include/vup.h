@@ -26,7 +26,8 @@
  *    device array behind vup_marginalize_noalloc (VUP_NOALLOC_SCRATCH_BYTES
  *    per GPU, part of the loaded code object, never allocated by a call).
  *  - Streams: every kernel is enqueued on `stream` (a hipStream_t; NULL = the
- *    default stream). No call synchronises except vup_counters.
+ *    default stream). No call synchronises except vup_counters and
+ *    vup_set_sweep_mode with VUP_SWEEP_AUTO.
  *  - Errors: every call returns VUP_OK (0) or a negative status. Arguments
  *    that can be checked on the host are checked before anything is enqueued;
  *    on failure nothing is enqueued and vup_last_error() (thread-local)
