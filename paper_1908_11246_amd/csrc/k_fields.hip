@@ -784,16 +784,30 @@ __global__ __launch_bounds__(256) void k_marg_partial(const float* __restrict__ 
   part[(long long)blockIdx.y * n + j] = acc;
 }
 
-// out[j] = sum over chunks of part[chunk][j], in a fixed order: a workgroup
-// takes 16 columns (128-byte pieces of the partial sums' rows), its thread
-// (x, y) column x of chunks y, y + 32, ..., eight loads in flight; then the 32
-// sums of a column are added in order. A wave per column with a chunk per lane
-// read 8 bytes of each line (7.6 us at 1024 chunks of 512 columns, 3.9 us so).
-__global__ __launch_bounds__(512) void k_marg_combine(const double* __restrict__ part, int chunks,
-                                                      int n, double* __restrict__ out) {
-  __shared__ double sums[32][17];
-  const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
-  const int j = blockIdx.x * 16 + x;
+// out[j] = sum over chunks of part[chunk][j], in a fixed order: a wave per
+// column, lanes take chunks lane, lane + 64, ..., and the wave sum. Bound by
+// the latency of its few loads: 1.8 us at 38 chunks, 2.5 at 250.
+__global__ __launch_bounds__(64) void k_marg_combine(const double* __restrict__ part, int chunks,
+                                                     int n, double* __restrict__ out) {
+  const int j = blockIdx.x;
+  double s = 0.0;
+#pragma unroll 8
+  for (int c = threadIdx.x; c < chunks; c += 64) s += part[(long long)c * n + j];
+  s = wave_sum(s);
+  if (threadIdx.x == 0) out[j] = s;
+}
+
+// The same for many chunks of many columns, where a wave per column reads 8
+// bytes of each line: a workgroup takes 16 columns (128-byte pieces of the
+// partial sums' rows), its thread (x, y) column x of chunks y, y + 32, ...,
+// eight loads in flight; then the 32 sums of a column are added in order.
+constexpr int kMargWide = 16;
+__global__ __launch_bounds__(512) void k_marg_combine_wide(const double* __restrict__ part,
+                                                           int chunks, int n,
+                                                           double* __restrict__ out) {
+  __shared__ double sums[32][kMargWide + 1];
+  const int x = threadIdx.x & (kMargWide - 1), y = threadIdx.x / kMargWide;
+  const int j = blockIdx.x * kMargWide + x;
   double s = 0.0;
   if (j < n) {
 #pragma unroll 8
@@ -808,6 +822,15 @@ __global__ __launch_bounds__(512) void k_marg_combine(const double* __restrict__
   }
 }
 
+// Which of the two, measured (us, wave per column > 16 columns): the second
+// one's barrier and its chain of 32 adds cost more than the lines it saves
+// while chunks are few (250 chunks: 2.8 > 3.6 at n = 8, 3.3 > 4.9 at 128,
+// 3.6 > 4.6 at 512, 4.1 > 4.8 at 1000) or columns are (2048 chunks: 2.5 > 5.2
+// at n = 1, 5.0 > 5.1 at 16, 6.2 > 5.6 at 64, 5.5 > 6.6 at 100); beyond both it
+// wins (2048 chunks: 6.8 > 6.1 at n = 128, 8.2 > 6.1 at 256; 1024: 7.2 > 4.4 at
+// 512; 512: 5.9 > 3.9 at 1000).
+static bool marg_wide(int chunks, int n) { return chunks >= 512 && n >= 128; }
+
 hipError_t launch_marginalize(int64_t K, int n, const float* A, const double* rho, void* ws,
                               double* out, hipStream_t s) {
   if (n == 0) return hipSuccess;
@@ -821,8 +844,11 @@ hipError_t launch_marginalize(int64_t K, int n, const float* A, const double* rh
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_marg_combine, dim3((unsigned)((n + 15) / 16)), dim3(512), 0, s, part,
-                     chunks, n, out);
+  if (marg_wide(chunks, n))
+    hipLaunchKernelGGL(k_marg_combine_wide, dim3((unsigned)((n + kMargWide - 1) / kMargWide)),
+                       dim3(512), 0, s, part, chunks, n, out);
+  else
+    hipLaunchKernelGGL(k_marg_combine, dim3((unsigned)n), dim3(64), 0, s, part, chunks, n, out);
   return hipGetLastError();
 }
 

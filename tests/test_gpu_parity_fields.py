@@ -290,6 +290,21 @@ def test_marginal(vup, K, n):
     _say(f"[marginal K={K} n={n}] ok, workspace {vup.marginal_workspace_bytes(K, n)} B")
 
 
+@pytest.mark.parametrize("K,n", [(K, n) for K in (4088, 4089, 4096, 4104)
+                                 for n in (127, 128, 129, 144, 256)] + [(9000, 257), (20000, 1)])
+def test_marginal_where_the_second_pass_changes_form(vup, K, n):
+    """Around 512 chunks (8 rows each) and 128 columns. Every term is positive,
+    so either side's K additions in FP64 are within K 2^-53 of the sum."""
+    rng = np.random.Generator(np.random.PCG64(K * 7 + n))
+    A = rng.random((K, n)).astype(np.float32)
+    rho = rng.random(K)
+    At, rt = torch.from_numpy(A).to(DEV), torch.from_numpy(rho).to(DEV)
+    got = vup.marginalize(At, rt)
+    np.testing.assert_allclose(_cpu(got), ofields.marginalize(A, rho), rtol=2 * K * 2.0 ** -53,
+                               atol=0)
+    assert torch.equal(got, vup.marginalize(At, rt))
+
+
 def test_marginal_empty_and_workspace_errors(vup):
     out = vup.marginalize(torch.zeros((0, 5), dtype=torch.float32, device=DEV))
     assert torch.equal(out, torch.zeros(5, dtype=torch.float64, device=DEV))
