@@ -250,7 +250,7 @@ def ipsa_views(vup, mm, P, mu, sigma, stream, reps):
         "marginalize_Q": (_c_call(vup, "vup_marginalize", K, n_dy, v(Q), None, v(ws),
                                   ws.numel(), v(g_out), sp),
                           K * n_dy * 4 + 2 * chunks_bytes + n_dy * 8,
-                          "k_marg_partial + k_marg_combine"),
+                          "k_marg_partial + k_marg_combine_wide"),
     }
     # Bayes inversion (Sec. 3) for 64 distributions spread over K: 64 x N FP32
     # posteriors plus per-bin posterior means
